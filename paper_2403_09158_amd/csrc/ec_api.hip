@@ -298,6 +298,7 @@ struct ec_state {
   // between hops, gets it stored at once instead of formed twice).
   bool sig_lazy = false;
   bool whole_read = false;  // the whole field was needed since the last solve
+  double volume = 0.0;      // footprint volume of the list, voxels (list_volume)
   std::vector<DevDefect> hdefs;
   std::vector<int32_t> hcnt;  // host copy of the counts, valid when hcnt_ok
   bool hcnt_ok = false;
@@ -937,13 +938,14 @@ ec_status join_self(ec_state* st, hipStream_t s);
 ec_status pipeline(ec_state* st, hipStream_t s, bool fp64, const int32_t* own, const int2* lnk, const DevDefect* defs,
                    int ndef, void* spec, double* sig, const double* add6, uint32_t* ctr,
                    const std::function<ec_status()>& between = {}, const double* bg = nullptr, int bg_mask = 0,
-                   const double* bg3 = nullptr, bool covered_only = false) {
+                   const double* bg3 = nullptr, bool covered_only = false, bool sparse = false) {
   const Prune full{0, st->n, 0, st->n};
   const double sb = spec_valid_bytes(st, fp64), fb = 48.0 * (double)st->n3;
   SpecGeom g{st->n, 0};
   g.P = spec_pitch(st->n, fp64);
   LAUNCH(st, s, PF_XF, 4.0 * (double)st->n3 + sb,
-         launch_x_forward(fp64, own, lnk, defs, ndef, nullptr, spec, g, st->tw, ctr, s));
+         sparse ? launch_x_forward_rows(own, lnk, defs, ndef, (double2*)spec, g, st->tw, ctr, s)
+                : launch_x_forward(fp64, own, lnk, defs, ndef, nullptr, spec, g, st->tw, ctr, s));
   LAUNCH(st, s, PF_Y, 2 * sb, launch_pencil(fp64, false, 1, spec, g, full, st->tw, ctr ? ctr : nullptr, s));
   if (between) {
     const ec_status r = between();
@@ -1079,7 +1081,8 @@ ec_status ensure_window(ec_state* st, int Dneed, hipStream_t s) {
     for (int b = 0; b < 6; ++b) {
       HIPCHK(launch_fill_i32((int32_t*)own, 1, b, s));  // voxel 0 owned by unit defect b
       ec_status q =
-          pipeline(st, s, true, (const int32_t*)own, dlnk, dunit, 6, sp, (double*)sg, (const double*)ad + 8 * b, nullptr);
+          pipeline(st, s, true, (const int32_t*)own, dlnk, dunit, 6, sp, (double*)sg, (const double*)ad + 8 * b, nullptr, {},
+                   nullptr, 0, nullptr, false, true);
       if (q != EC_OK) return q;
       HIPCHK(launch_window_crop((const double*)sg, n, D, b, (double*)K, s));
     }
@@ -1462,6 +1465,22 @@ void frame_maps(const double* A, double* out) {
   for (int k = 0; k < 9; ++k) out[72 + k] = A[k];
 }
 
+// Volume of a list's footprints in voxels, from the shapes (disk times
+// thickness, ball), overlaps counted once per defect.
+double list_volume(const DevDefect* h, int ndef) {
+  double v = 0.0;
+  for (int i = 0; i < ndef; ++i) {
+    const double r2 = (double)h[i].R2q / ((double)QSUB * QSUB);
+    v += h[i].kind == EC_LOOP ? M_PI * r2 * h[i].eq / QSUB : 4.0 / 3.0 * M_PI * r2 * std::sqrt(r2);
+  }
+  return v;
+}
+
+// Whether a solve's x forward pass sums its rows directly over the covered
+// voxels (launch_x_forward_rows): FP64 storage and a list that fills a small
+// part of the cell.
+bool sparse_rows(const ec_state* st) { return st->fp64 && st->volume < rows_limit(st->n) * (double)st->n3; }
+
 // Commits the quantised list h (ndef entries in the pinned staging buffer of
 // the device table, pin_begin already called on it) and solves: footprint
 // slots from the box volumes, the old eigenstrain out and the new one in, the
@@ -1500,6 +1519,8 @@ ec_status solve_table(ec_state* st, DevDefect* h, int32_t ndef, hipStream_t s, b
   }
   // commit: remove the old eigenstrain, add the new one
   if ((r = join_self(st, s)) != EC_OK) return r;
+  // a list moved on the device keeps its shapes and so its volume
+  if (h) st->volume = list_volume(h, ndef);
   const DefBuf& ob = st->db[st->cur];
   if (st->ndef > 0)
     LAUNCH(st, s, PF_RASTER, 0, launch_unraster(ob.tab, st->ndef, ob.cnt, ob.ids, st->own, s));
@@ -1543,7 +1564,7 @@ ec_status solve_table(ec_state* st, DevDefect* h, int32_t ndef, hipStream_t s, b
   // the stress of dislocation lines, if any, is added by the x inverse pass
   const bool covered = !st->whole_read;
   r = pipeline(st, s, st->fp64, st->own, nb.lnk, nb.tab, ndef, st->spec, st->sig, st->add6, st->tilectr, beside, st->bg,
-               st->bg_mask, st->bg3_on ? st->bg3 : nullptr, covered);
+               st->bg_mask, st->bg3_on ? st->bg3 : nullptr, covered, sparse_rows(st));
   if (r != EC_OK) return r;
   st->solved = true;
   st->sig_lazy = covered;

@@ -349,6 +349,11 @@ constexpr int NTILECTR = 24;
 hipError_t launch_x_forward(bool fp64, const int32_t* own, const int2* lnk, const DevDefect* defs, int ndef,
                             const double* dense, void* spec, SpecGeom g, const double2* tw, uint32_t* zero_ctr,
                             hipStream_t s);
+// The same from owner lists by direct row sums (FP64 storage), for lists whose
+// volume is below rows_limit(n) n^3 voxels.
+double rows_limit(int n);
+hipError_t launch_x_forward_rows(const int32_t* own, const int2* lnk, const DevDefect* defs, int ndef, double2* spec,
+                                 SpecGeom g, const double2* tw, uint32_t* zero_ctr, hipStream_t s);
 // Energies of a stored defect type at up to TYPE_NP translated positions per
 // launch (Sec. 3.3): sig, te, ts are the half spectra of the field, of the
 // type's eigenstrain and of its stress; tab/nyq the phase tables of the np

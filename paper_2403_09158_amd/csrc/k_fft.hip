@@ -427,6 +427,133 @@ __global__ __launch_bounds__(pick_T(max_nb(N, 3 * x_rows(N)))) void k_x_forward(
   }
 }
 
+// The x forward pass for eigenstrain fields that few voxels carry: one
+// wavefront per row, a lane per kx, and the row transform summed directly,
+// X(kx) = sum_x eps*(x) W^(kx x), over the row's covered voxels in ascending x.
+// Each piece of 64 voxels is packed by ballot: its covered lanes leave their
+// eigenstrains side by side in LDS (single owners fetched for all pieces in
+// one round trip), where the sum reads them as broadcasts.  The Nyquist column
+// of an even N (W^(N x / 2) = +-1) is summed beside the others.  One row per
+// wavefront, not a loop over rows: a wave's memory counter completes in issue
+// order, so the next row's links would wait for this row's stores.
+//
+// FP64 storage only: with FP32 storage a last-bit difference from the
+// transforms moves the rounding of a spectrum value now and then, and the
+// later passes spread that over the whole field at the level of the storage
+// error.  At 129^3, 300 defects, the pass takes 19 us (transforms: 170, bound by
+// the length-43 butterflies), at 256^3, 2000 defects, 222 (236; 811 MB written).
+template <int N>
+__global__ __launch_bounds__(256) void k_x_forward_rows(const int32_t* __restrict__ own, const int2* __restrict__ lnk,
+                                                        const DevDefect* __restrict__ defs,
+                                                        double2* __restrict__ spec,
+                                                        const double2* __restrict__ twg,
+                                                        uint32_t* __restrict__ zero_ctr, int max_links) {
+  constexpr int P = spec_pitch(N, true);
+  constexpr int NC = (N + 63) / 64;                  // pieces of 64 voxels of a row
+  constexpr bool EVEN = N % 2 == 0;
+  constexpr int NK = EVEN ? N / 2 : N / 2 + 1;       // columns on the lanes
+  constexpr int NQ = (NK + 63) / 64;                 // columns per lane
+  __shared__ double2 tw[N + N / 16 + 1];
+  __shared__ double2 stage_out[4][64 * 6];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  // contiguous ranges of rows per XCD (workgroup b on XCD b % 8), four rows per workgroup
+  constexpr int per = ((N * N + 3) / 4 + 7) / 8;
+  const int row = ((int)(blockIdx.x % 8) * per + (int)(blockIdx.x / 8)) * 4 + wave;
+  const bool live = (int)(blockIdx.x / 8) < per && row < N * N;
+  int32_t link[NC];
+#pragma unroll
+  for (int j = 0; j < NC; ++j) {
+    const int x = 64 * j + lane;
+    link[j] = live && x < N ? own[(size_t)row * N + x] : -1;
+  }
+  for (int i = threadIdx.x; i < N; i += 256) tw[i + (i >> 4)] = twg[i];
+  if (zero_ctr && blockIdx.x == 0 && threadIdx.x < NTILECTR) zero_ctr[threadIdx.x] = 0u;
+  double2 ev[NC][3];
+#pragma unroll
+  for (int j = 0; j < NC; ++j) {
+    if (link[j] >= 0) {
+      const double2* f = reinterpret_cast<const double2*>(defs[link[j]].efd);
+#pragma unroll
+      for (int p = 0; p < 3; ++p) ev[j][p] = f[p];
+    }
+  }
+  __syncthreads();
+  if (!live) return;
+  double2* const st = stage_out[wave];  // a piece's eigenstrains, three entries each; then a row's bins
+  double2 acc[NQ][6];
+  double nyq[6];
+#pragma unroll
+  for (int c = 0; c < 6; ++c) {
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) acc[q][c] = make_double2(0.0, 0.0);
+    nyq[c] = 0.0;
+  }
+#pragma unroll
+  for (int j = 0; j < NC; ++j) {
+    const bool in = link[j] != -1;
+    uint64_t m = __ballot(in);
+    if (m == 0) continue;
+    if (in) {
+      const int k = __popcll(m & ((1ull << lane) - 1));
+      if (link[j] < -1) {  // several owners: the exact sum over the chain
+        double e[6];
+        decode_voxel(link[j], lnk, defs, e, max_links);
+#pragma unroll
+        for (int p = 0; p < 3; ++p) ev[j][p] = make_double2(e[2 * p], e[2 * p + 1]);
+      }
+#pragma unroll
+      for (int p = 0; p < 3; ++p) st[3 * k + p] = ev[j][p];
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    for (int k = 0; m; ++k) {
+      const int x = 64 * j + __ffsll((unsigned long long)m) - 1;
+      m &= m - 1;
+      double e[6];
+#pragma unroll
+      for (int p = 0; p < 3; ++p) {
+        const double2 v = st[3 * k + p];
+        e[2 * p] = v.x;
+        e[2 * p + 1] = v.y;
+      }
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) {
+        const int i = ((lane + 64 * q) * x) % N;
+        const double2 f = tw[i + (i >> 4)];
+#pragma unroll
+        for (int c = 0; c < 6; ++c) {
+          acc[q][c].x = fma(e[c], f.x, acc[q][c].x);
+          acc[q][c].y = fma(e[c], f.y, acc[q][c].y);
+        }
+      }
+      if constexpr (EVEN) {
+#pragma unroll
+        for (int c = 0; c < 6; ++c) nyq[c] += (x & 1) ? -e[c] : e[c];
+      }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  }
+  // a lane's six values turned into runs of 16 bytes per lane over the wavefront
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) {
+#pragma unroll
+    for (int c = 0; c < 6; ++c) st[6 * lane + c] = acc[q][c];
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    const int cnt = 6 * (NK - 64 * q < 64 ? NK - 64 * q : 64);
+    double2* const out = spec + ((size_t)row * P + 64 * q) * 6;
+#pragma unroll
+    for (int i = 0; i < 6; ++i)
+      if (lane + 64 * i < cnt) out[lane + 64 * i] = st[lane + 64 * i];
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  }
+  if constexpr (EVEN) {
+    if (lane == 0) {
+      double2* const out = spec + ((size_t)row * P + NK) * 6;
+#pragma unroll
+      for (int c = 0; c < 6; ++c) out[c] = make_double2(nyq[c], 0.0);
+    }
+  }
+}
+
 // Update variant: the rows of the eigenstrain change
 // dE = E_new chi_new - E_old chi_old (E: E_old in [0, 6), E_new in [6, 12))
 // are built in LDS from the two footprint lists (new ids = old ids shifted by
@@ -1180,6 +1307,15 @@ hipError_t go_xf(const int32_t* own, const int2* lnk, const DevDefect* defs, int
   return hipGetLastError();
 }
 
+template <int N>
+hipError_t go_xr(const int32_t* own, const int2* lnk, const DevDefect* defs, int ndef, double2* spec, SpecGeom g,
+                 const double2* tw, uint32_t* zero_ctr, hipStream_t s) {
+  if (g.P != spec_pitch(N, true)) return hipErrorInvalidValue;
+  const int grid = (((N * N + 3) / 4 + 7) / 8) * 8;
+  hipLaunchKernelGGL(k_x_forward_rows<N>, dim3(grid), dim3(256), 0, s, own, lnk, defs, spec, tw, zero_ctr, ndef);
+  return hipGetLastError();
+}
+
 template <int N, typename S>
 hipError_t go_xf_vm(const double* vm, void* spec, SpecGeom g, const double2* tw, hipStream_t s) {
   constexpr int T = pick_T(max_nb(N, 3 * x_rows(N)));
@@ -1314,6 +1450,15 @@ bool fft_supported(int n) {
   }
 }
 
+// Up to this part of the cell's voxels the direct row sums of the x forward
+// pass beat its transforms.  The sums cost a fixed share per covered voxel, the
+// transforms nothing more: us for the pass with rows / with transforms, at 0.5,
+// 2.1 and 4.2 % covered: 256^3 188 / 222, 222 / 236, 234 / 260; at 3.2 % of
+// 240^3 204 / 225; past that the transforms win (6.4 % of 160^3: 65 / 61, 21 %
+// of 128^3: 50 / 42).  Where the transform has a direct large radix the sums win
+// by far (129^3: 21 / 171 at 0.6 %, 32 / 175 at 5 %).
+double rows_limit(int n) { return n == 129 ? 0.5 : 0.04; }
+
 int pencil_width(int n, bool) { return n >= 512 ? 8 : 16; }
 
 hipError_t launch_x_forward(bool fp64, const int32_t* own, const int2* lnk, const DevDefect* defs, int ndef,
@@ -1324,6 +1469,18 @@ hipError_t launch_x_forward(bool fp64, const int32_t* own, const int2* lnk, cons
   case NN:                                                                              \
     return fp64 ? go_xf<NN, double>(own, lnk, defs, ndef, dense, spec, g, tw, zero_ctr, s) \
                 : go_xf<NN, float>(own, lnk, defs, ndef, dense, spec, g, tw, zero_ctr, s);
+    EC_FOR_SIZES(EC_CASE)
+#undef EC_CASE
+  }
+  return hipErrorInvalidValue;
+}
+
+hipError_t launch_x_forward_rows(const int32_t* own, const int2* lnk, const DevDefect* defs, int ndef, double2* spec,
+                                 SpecGeom g, const double2* tw, uint32_t* zero_ctr, hipStream_t s) {
+  switch (g.n) {
+#define EC_CASE(NN) \
+  case NN:          \
+    return go_xr<NN>(own, lnk, defs, ndef, spec, g, tw, zero_ctr, s);
     EC_FOR_SIZES(EC_CASE)
 #undef EC_CASE
   }
