@@ -2650,6 +2650,11 @@ ec_status ec_set_dislocations(ec_state* st, const ec_line* lines, int32_t nlines
   return EC_OK;
 }
 
+// Pieces from which on the paths' spectrum is formed on the grid (below, the sum
+// over the pieces at every bin takes less than the transforms), and up to which
+// its scratch is asked for (2 KB a piece beside two FP64 half spectra).
+constexpr size_t PATH_POINTS_MIN = 96, PATH_POINTS_MAX = 131072;
+
 ec_status ec_set_dislocation_paths(ec_state* st, const ec_path* paths, int32_t npaths, const double* verts,
                                    int32_t nverts, void* stream) {
   if (!st) return fail(EC_ERR_ARG, "state is NULL");
@@ -2742,22 +2747,40 @@ ec_status ec_set_dislocation_paths(ec_state* st, const ec_path* paths, int32_t n
                           0.5 * (Ubar[1] + Ubar[3])};
     neg_C_dot(st, e6, mean6);
   }
+  // many pieces: the spread Nye tensor transformed on the grid, where its
+  // scratch fits the budget; else summed piece by piece at every bin
+  Tmp ts{st->ctx};
+  double mmax = 0.0;
+  for (const DevPiece& pc : pieces)
+    for (double v : pc.M) mmax = std::max(mmax, std::fabs(v));
+  bool points = pieces.size() >= PATH_POINTS_MIN && pieces.size() <= PATH_POINTS_MAX && mmax > 0.0 &&
+                std::ilogb(mmax) > -900 && std::ilogb(mmax) < 900;
+  if (points && ledger_alloc(st->ctx, ts.b = path_scratch(n, (int)pieces.size()).bytes, &ts.p) != EC_OK) {
+    ts.b = 0;
+    points = false;
+  }
   HIPCHK(hipStreamSynchronize(s));
   HIPCHK(hipMemcpy(tp.p, pieces.data(), tp.b, hipMemcpyHostToDevice));
   HIPCHK(hipMemcpy(tm.p, mean6, 64, hipMemcpyHostToDevice));
   if ((r = join_self(st, s)) != EC_OK) return r;
-  // take the old paths' stress out of the resident field, put the new one in
-  if (st->solved && st->bg3_on) LAUNCH(st, s, PF_OTHER, 0, launch_bg3_add(st->sig, st->bg3, st->n3, -1.0, s));
-  st->bg3_on = false;
   const bool fp64 = st->fp64;
   const Prune full{0, n, 0, n};
+  const int np = (int)pieces.size();
   LAUNCH(st, s, PF_OTHER, 0,
-         launch_path_spectrum(fp64, (const DevPiece*)tp.p, (int)pieces.size(), st->g, L, st->C, st->tw, st->spec, s));
+         points ? launch_path_points(fp64, (const DevPiece*)tp.p, np, std::ldexp(1.0, 61 - std::ilogb(mmax)), st->g, L,
+                                     st->C, st->tw, (char*)ts.p, st->spec, s)
+                : launch_path_spectrum(fp64, (const DevPiece*)tp.p, np, st->g, L, st->C, st->tw, st->spec, s));
   LAUNCH(st, s, PF_Z, 0, launch_pencil(fp64, true, 2, st->spec, st->g, full, st->tw, nullptr, s));
   LAUNCH(st, s, PF_Y, 0, launch_pencil(fp64, true, 1, st->spec, st->g, full, st->tw, nullptr, s));
-  LAUNCH(st, s, PF_XI, 0, launch_x_inverse(fp64, false, st->spec, st->bg3, st->g, (const double*)tm.p, st->tw, s));
+  // the new paths' stress, and the old one's place in the resident field taken by it
+  if (st->solved && st->bg3_on) {
+    LAUNCH(st, s, PF_XI, 0,
+           launch_x_inverse_swap(fp64, st->spec, st->bg3, st->sig, st->g, (const double*)tm.p, st->tw, s));
+  } else {
+    LAUNCH(st, s, PF_XI, 0, launch_x_inverse(fp64, false, st->spec, st->bg3, st->g, (const double*)tm.p, st->tw, s));
+    if (st->solved) LAUNCH(st, s, PF_OTHER, 0, launch_bg3_add(st->sig, st->bg3, st->n3, 1.0, s));
+  }
   st->bg3_on = true;
-  if (st->solved) LAUNCH(st, s, PF_OTHER, 0, launch_bg3_add(st->sig, st->bg3, st->n3, 1.0, s));
   st->jdE_ok = false;
   HIPCHK(hipStreamSynchronize(s));  // the piece table is freed on return
   return EC_OK;

@@ -389,6 +389,29 @@ hipError_t launch_bg_add(double* sig, const double* planes, int mask, int n, dou
 // (xi = 0 left at zero), written into spec in the state's storage precision.
 hipError_t launch_path_spectrum(bool fp64, const DevPiece* pieces, int np, SpecGeom g, double L, Cubic C,
                                 const double2* tw, void* spec, hipStream_t s);
+// The same from the Nye tensor spread on the grid and transformed, for many
+// pieces: scratch as path_scratch lays it out; scale a power of two with
+// |M| scale < 2^62 for every piece.
+struct PathScratch {
+  size_t a, b, map, sums, vals, bytes;
+};
+inline PathScratch path_scratch(int n, int np) {
+  const size_t spec = (size_t)6 * n * n * spec_pitch(n, true) * 16;
+  PathScratch p;
+  p.a = 0;
+  p.b = p.a + spec;
+  p.map = p.b + spec;
+  p.sums = p.map + (((size_t)n * n * n * 4 + 255) / 256) * 256;
+  p.vals = p.sums + (size_t)8 * np * 18 * 8;
+  p.bytes = p.vals + (size_t)8 * np * 12 * 8;
+  return p;
+}
+hipError_t launch_path_points(bool fp64, const DevPiece* pieces, int np, double scale, SpecGeom g, double L, Cubic C,
+                              const double2* tw, char* scratch, void* spec, hipStream_t s);
+// The x row sums of grid points: map[v] names the record vals + map[v] stride
+// (six doubles), -1 none.
+hipError_t launch_x_forward_points(const int32_t* map, const double* vals, int stride, double2* spec, SpecGeom g,
+                                   const double2* tw, hipStream_t s);
 // sig[v][c] += sgn * bg3[v][c] over n^3 voxels (a 3-D background stress).
 hipError_t launch_bg3_add(double* sig, const double* bg3, int64_t n3, double sgn, hipStream_t s);
 hipError_t launch_green(bool fp64, void* spec, SpecGeom g, Cubic C, hipStream_t s);
@@ -402,6 +425,10 @@ hipError_t launch_z_green(bool fp64, void* spec, SpecGeom g, Cubic C, Prune pr, 
 hipError_t launch_x_inverse(bool fp64, bool accum, const void* spec, double* sig, SpecGeom g, const double* mean6,
                             const double2* tw, hipStream_t s, const double* bg = nullptr, int bg_mask = 0,
                             const double* add3 = nullptr, const int32_t* own = nullptr, bool all = false);
+// The x inverse pass into part, a stress that total contains, and total renewed
+// with it: total = (total - old part) + new part.
+hipError_t launch_x_inverse_swap(bool fp64, const void* spec, double* part, double* total, SpecGeom g,
+                                 const double* mean6, const double2* tw, hipStream_t s);
 // The Fourier passes of a batch of hops (jobs: njob device records, see
 // HopJob; ctr: NTILECTR tile counters, zeroed by the first pass): sparse x
 // forward, pruned y forward, fused z pass, y inverse, accumulating x inverse

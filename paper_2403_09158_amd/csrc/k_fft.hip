@@ -437,6 +437,9 @@ __global__ __launch_bounds__(pick_T(max_nb(N, 3 * x_rows(N)))) void k_x_forward(
 // wavefront, not a loop over rows: a wave's memory counter completes in issue
 // order, so the next row's links would wait for this row's stores.
 //
+// A link >= 0 names the record vals + link stride of six doubles (a defect's
+// eigenstrain, or the values of a grid point of dislocation pieces).
+//
 // FP64 storage only: with FP32 storage a last-bit difference from the
 // transforms moves the rounding of a spectrum value now and then, and the
 // later passes spread that over the whole field at the level of the storage
@@ -445,6 +448,7 @@ __global__ __launch_bounds__(pick_T(max_nb(N, 3 * x_rows(N)))) void k_x_forward(
 template <int N>
 __global__ __launch_bounds__(256) void k_x_forward_rows(const int32_t* __restrict__ own, const int2* __restrict__ lnk,
                                                         const DevDefect* __restrict__ defs,
+                                                        const double* __restrict__ vals, int stride,
                                                         double2* __restrict__ spec,
                                                         const double2* __restrict__ twg,
                                                         uint32_t* __restrict__ zero_ctr, int max_links) {
@@ -472,7 +476,7 @@ __global__ __launch_bounds__(256) void k_x_forward_rows(const int32_t* __restric
 #pragma unroll
   for (int j = 0; j < NC; ++j) {
     if (link[j] >= 0) {
-      const double2* f = reinterpret_cast<const double2*>(defs[link[j]].efd);
+      const double2* f = reinterpret_cast<const double2*>(vals + (size_t)link[j] * stride);
 #pragma unroll
       for (int p = 0; p < 3; ++p) ev[j][p] = f[p];
     }
@@ -1162,12 +1166,14 @@ __global__ __launch_bounds__(256) void k_green(typename Cplx<S>::T* __restrict__
 // held.  keep = 0 stores every voxel: the pass that forms the whole field runs
 // this same code, so a covered voxel gets the same bits either way (separate
 // code for the two could fuse multiplies and adds differently).
-template <int N, typename S, bool ACC, bool BG, bool BATCH = false, bool MASK = false>
+// SWAP (with ACC): the stress replaces the one in sig, and the total it is part
+// of is renewed with it, total = (total - old) + new.
+template <int N, typename S, bool ACC, bool BG, bool BATCH = false, bool MASK = false, bool SWAP = false>
 __global__ __launch_bounds__(pick_T(max_nb(N, 3 * x_rows(N)))) void k_x_inverse(
     const typename Cplx<S>::T* __restrict__ spec, double* __restrict__ sig, const double* __restrict__ mean6,
     const double2* __restrict__ twg, const double* __restrict__ bg, int bg_mask,
     const HopJob* __restrict__ jobs = nullptr, const double* add3 = nullptr,
-    const int32_t* __restrict__ own = nullptr, int32_t keep = -1) {
+    const int32_t* __restrict__ own = nullptr, int32_t keep = -1, double* total = nullptr) {
   constexpr int ROWS = x_rows(N);
   constexpr int NF = 3 * ROWS;
   constexpr int T = pick_T(max_nb(N, NF));
@@ -1240,8 +1246,14 @@ __global__ __launch_bounds__(pick_T(max_nb(N, 3 * x_rows(N)))) void k_x_inverse(
   if constexpr (ACC)
     for_outputs<N, RL, NSL, Map::Row, NF, T>([&](int f, int x, int slot) {
       if (!MASK || ow[slot] != -1)
+      {
         old[slot] = add_at(f, x);
-      else
+        if constexpr (SWAP) {  // the total without the old stress
+          const int p = f % 3, y = y0 + f / 3;
+          const double2 t = *reinterpret_cast<const double2*>(total + (6 * ((z * N + y) * N + x) + 2 * p));
+          old[slot] = make_double2(t.x - old[slot].x, t.y - old[slot].y);
+        }
+      } else
         old[slot] = make_double2(0.0, 0.0);
     });
   auto store_last = [&](int f, int x, double2 v, int slot) {
@@ -1250,7 +1262,10 @@ __global__ __launch_bounds__(pick_T(max_nb(N, 3 * x_rows(N)))) void k_x_inverse(
     const int p = f % 3, y = y0 + f / 3;
     double2* s01 = sig_at(f, x);
     double2 r = make_double2(v.x * scale + mean_s[2 * p], v.y * scale + mean_s[2 * p + 1]);
-    if constexpr (ACC) {
+    if constexpr (SWAP) {
+      const double2 o = old[slot];
+      *reinterpret_cast<double2*>(total + (6 * ((z * N + y) * N + x) + 2 * p)) = make_double2(o.x + r.x, o.y + r.y);
+    } else if constexpr (ACC) {
       const double2 o = old[slot];
       r.x += o.x;
       r.y += o.y;
@@ -1308,11 +1323,12 @@ hipError_t go_xf(const int32_t* own, const int2* lnk, const DevDefect* defs, int
 }
 
 template <int N>
-hipError_t go_xr(const int32_t* own, const int2* lnk, const DevDefect* defs, int ndef, double2* spec, SpecGeom g,
-                 const double2* tw, uint32_t* zero_ctr, hipStream_t s) {
+hipError_t go_xr(const int32_t* own, const int2* lnk, const DevDefect* defs, int ndef, const double* vals, int stride,
+                 double2* spec, SpecGeom g, const double2* tw, uint32_t* zero_ctr, hipStream_t s) {
   if (g.P != spec_pitch(N, true)) return hipErrorInvalidValue;
   const int grid = (((N * N + 3) / 4 + 7) / 8) * 8;
-  hipLaunchKernelGGL(k_x_forward_rows<N>, dim3(grid), dim3(256), 0, s, own, lnk, defs, spec, tw, zero_ctr, ndef);
+  hipLaunchKernelGGL(k_x_forward_rows<N>, dim3(grid), dim3(256), 0, s, own, lnk, defs, vals, stride, spec, tw,
+                     zero_ctr, ndef);
   return hipGetLastError();
 }
 
@@ -1390,6 +1406,17 @@ hipError_t go_xi(bool acc, const void* spec, double* sig, SpecGeom g, const doub
     go_xi_k<N, S, false, true>(spec, sig, mean6, tw, bg, bg_mask, nullptr, own, all, s);
   else
     go_xi_k<N, S, false, false>(spec, sig, mean6, tw, bg, 0, nullptr, own, all, s);
+  return hipGetLastError();
+}
+
+template <int N, typename S>
+hipError_t go_xi_swap(const void* spec, double* part, double* total, SpecGeom g, const double* mean6,
+                      const double2* tw, hipStream_t s) {
+  constexpr int T = pick_T(max_nb(N, 3 * x_rows(N)));
+  if (g.P != spec_pitch(N, sizeof(S) == 8)) return hipErrorInvalidValue;
+  hipLaunchKernelGGL((k_x_inverse<N, S, true, false, false, false, true>), dim3(N * (N / x_rows(N))), dim3(T), 0, s,
+                     (const typename Cplx<S>::T*)spec, part, mean6, tw, (const double*)nullptr, 0,
+                     (const HopJob*)nullptr, (const double*)nullptr, (const int32_t*)nullptr, 0, total);
   return hipGetLastError();
 }
 
@@ -1475,16 +1502,29 @@ hipError_t launch_x_forward(bool fp64, const int32_t* own, const int2* lnk, cons
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_x_forward_rows(const int32_t* own, const int2* lnk, const DevDefect* defs, int ndef, double2* spec,
-                                 SpecGeom g, const double2* tw, uint32_t* zero_ctr, hipStream_t s) {
+static hipError_t x_rows_of(const int32_t* own, const int2* lnk, const DevDefect* defs, int ndef, const double* vals,
+                            int stride, double2* spec, SpecGeom g, const double2* tw, uint32_t* zero_ctr,
+                            hipStream_t s) {
   switch (g.n) {
 #define EC_CASE(NN) \
   case NN:          \
-    return go_xr<NN>(own, lnk, defs, ndef, spec, g, tw, zero_ctr, s);
+    return go_xr<NN>(own, lnk, defs, ndef, vals, stride, spec, g, tw, zero_ctr, s);
     EC_FOR_SIZES(EC_CASE)
 #undef EC_CASE
   }
   return hipErrorInvalidValue;
+}
+
+hipError_t launch_x_forward_rows(const int32_t* own, const int2* lnk, const DevDefect* defs, int ndef, double2* spec,
+                                 SpecGeom g, const double2* tw, uint32_t* zero_ctr, hipStream_t s) {
+  static_assert(sizeof(DevDefect) % 16 == 0 && offsetof(DevDefect, efd) % 16 == 0, "16-byte loads of efd");
+  return x_rows_of(own, lnk, defs, ndef, reinterpret_cast<const double*>(defs) + offsetof(DevDefect, efd) / 8,
+                   (int)(sizeof(DevDefect) / 8), spec, g, tw, zero_ctr, s);
+}
+
+hipError_t launch_x_forward_points(const int32_t* map, const double* vals, int stride, double2* spec, SpecGeom g,
+                                   const double2* tw, hipStream_t s) {
+  return x_rows_of(map, nullptr, nullptr, 0, vals, stride, spec, g, tw, nullptr, s);
 }
 
 hipError_t launch_x_forward_vm(bool fp64, const double* vm, void* spec, SpecGeom g, const double2* tw, hipStream_t s) {
@@ -1588,6 +1628,19 @@ hipError_t launch_x_inverse(bool fp64, bool accum, const void* spec, double* sig
   case NN:                                                                                       \
     return fp64 ? go_xi<NN, double>(accum, spec, sig, g, mean6, tw, bg, bg_mask, add3, own, all, s) \
                 : go_xi<NN, float>(accum, spec, sig, g, mean6, tw, bg, bg_mask, add3, own, all, s);
+    EC_FOR_SIZES(EC_CASE)
+#undef EC_CASE
+  }
+  return hipErrorInvalidValue;
+}
+
+hipError_t launch_x_inverse_swap(bool fp64, const void* spec, double* part, double* total, SpecGeom g,
+                                 const double* mean6, const double2* tw, hipStream_t s) {
+  switch (g.n) {
+#define EC_CASE(NN)                                                              \
+  case NN:                                                                       \
+    return fp64 ? go_xi_swap<NN, double>(spec, part, total, g, mean6, tw, s)     \
+                : go_xi_swap<NN, float>(spec, part, total, g, mean6, tw, s);
     EC_FOR_SIZES(EC_CASE)
 #undef EC_CASE
   }
@@ -1745,6 +1798,59 @@ __global__ __launch_bounds__(256) void k_bg_add(double* __restrict__ sig, const 
 // Nyquist bins the mean over the all -n/2 and all +n/2 representatives),
 // eps*_hat = sym(U_hat) and the Green step.  Pieces are staged in LDS in
 // chunks; one thread per bin.
+// sigma_hat (in e) of a bin from the nine components of its Nye tensor spectrum:
+// the distortion operator (Nyquist mean), sym(U), the Green step; zero at xi = 0.
+__device__ __forceinline__ void path_bin(const double2* al, int kx, int ky, int kz, int n, double L, const Cubic& C,
+                                         double2* e) {
+#pragma unroll
+  for (int c = 0; c < 6; ++c) e[c] = make_double2(0.0, 0.0);
+  const int k[3] = {kx, ky, kz};
+  if (kx != 0 || ky != 0 || kz != 0) {
+    const bool nyq = nyquist(kx, n) || nyquist(ky, n) || nyquist(kz, n);
+    const int nrep = nyq ? 2 : 1;
+    const double s2pi = 2.0 * M_PI / L;
+    double2 U[3][3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+      for (int j = 0; j < 3; ++j) U[i][j] = make_double2(0.0, 0.0);
+    for (int rep = 0; rep < nrep; ++rep) {
+      double x[3];
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        const int h = n / 2;
+        x[a] = s2pi * (nyquist(k[a], n) ? (rep == 0 ? -h : h) : centred(k[a], n));
+      }
+      const double q = 1.0 / ((x[0] * x[0] + x[1] * x[1] + x[2] * x[2]) * nrep);
+      // U_ij += -i (xi x alpha_i.)_j / |xi|^2, alpha_i. the row i of alpha_hat
+#pragma unroll
+      for (int i = 0; i < 3; ++i) {
+        const double2 a0 = al[3 * i], a1 = al[3 * i + 1], a2 = al[3 * i + 2];
+        const double2 c0 = make_double2(x[1] * a2.x - x[2] * a1.x, x[1] * a2.y - x[2] * a1.y);
+        const double2 c1 = make_double2(x[2] * a0.x - x[0] * a2.x, x[2] * a0.y - x[0] * a2.y);
+        const double2 c2 = make_double2(x[0] * a1.x - x[1] * a0.x, x[0] * a1.y - x[1] * a0.y);
+        // -i c = (c.y, -c.x)
+        U[i][0].x += q * c0.y;
+        U[i][0].y -= q * c0.x;
+        U[i][1].x += q * c1.y;
+        U[i][1].y -= q * c1.x;
+        U[i][2].x += q * c2.y;
+        U[i][2].y -= q * c2.x;
+      }
+    }
+    e[0] = U[0][0];
+    e[1] = U[1][1];
+    e[2] = U[2][2];
+    e[3] = make_double2(0.5 * (U[1][2].x + U[2][1].x), 0.5 * (U[1][2].y + U[2][1].y));
+    e[4] = make_double2(0.5 * (U[0][2].x + U[2][0].x), 0.5 * (U[0][2].y + U[2][0].y));
+    e[5] = make_double2(0.5 * (U[0][1].x + U[1][0].x), 0.5 * (U[0][1].y + U[1][0].y));
+    if (C.frm)
+      green_bin_rot(e, kx, ky, kz, n, C);
+    else
+      green_bin(e, kx, ky, kz, n, C);
+  }
+}
+
 constexpr int PATH_CHUNK = 128;
 
 template <typename S>
@@ -1792,52 +1898,76 @@ __global__ __launch_bounds__(256) void k_path_spectrum(const DevPiece* __restric
   }
   if (!live) return;
   double2 e[6];
+  path_bin(al, kx, ky, kz, n, L, C, e);
+  typename Cplx<S>::T* const out = spec + spec_at(kz, ky, kx, 0, n, P);
 #pragma unroll
-  for (int c = 0; c < 6; ++c) e[c] = make_double2(0.0, 0.0);
-  if (kx != 0 || ky != 0 || kz != 0) {
-    const bool nyq = nyquist(kx, n) || nyquist(ky, n) || nyquist(kz, n);
-    const int nrep = nyq ? 2 : 1;
-    const double s2pi = 2.0 * M_PI / L;
-    double2 U[3][3];
+  for (int c = 0; c < 6; ++c) st2(out + c, e[c]);
+}
+
+// The same spectrum for many pieces (launch_path_points): the spread Nye tensor
+// is formed on the grid, transformed, and taken through the operator per bin,
+// instead of summed piece by piece at every bin.
+//
+// One thread per piece and grid point around it.  The points in use get a
+// record each (map: the voxel's record, claimed by whichever comes first);
+// contributions are added there in fixed point, each value's low 32 bits and
+// the rest in sums of their own, so that the result is exact to 2^-62 of the
+// largest piece and does not depend on the order.
+__global__ __launch_bounds__(256) void k_piece_points(const DevPiece* __restrict__ pieces, int np, int n, double scale,
+                                                      int32_t* __restrict__ map, int64_t* __restrict__ sums) {
+  const int t = blockIdx.x * 256 + threadIdx.x;
+  if (t >= 8 * np) return;
+  const DevPiece& q = pieces[t / 8];
+  int v[3];
+  double w = 1.0;
 #pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-      for (int j = 0; j < 3; ++j) U[i][j] = make_double2(0.0, 0.0);
-    for (int rep = 0; rep < nrep; ++rep) {
-      double x[3];
-#pragma unroll
-      for (int a = 0; a < 3; ++a) {
-        const int h = n / 2;
-        x[a] = s2pi * (nyquist(k[a], n) ? (rep == 0 ? -h : h) : centred(k[a], n));
-      }
-      const double q = 1.0 / ((x[0] * x[0] + x[1] * x[1] + x[2] * x[2]) * nrep);
-      // U_ij += -i (xi x alpha_i.)_j / |xi|^2, alpha_i. the row i of alpha_hat
-#pragma unroll
-      for (int i = 0; i < 3; ++i) {
-        const double2 a0 = al[3 * i], a1 = al[3 * i + 1], a2 = al[3 * i + 2];
-        const double2 c0 = make_double2(x[1] * a2.x - x[2] * a1.x, x[1] * a2.y - x[2] * a1.y);
-        const double2 c1 = make_double2(x[2] * a0.x - x[0] * a2.x, x[2] * a0.y - x[0] * a2.y);
-        const double2 c2 = make_double2(x[0] * a1.x - x[1] * a0.x, x[0] * a1.y - x[1] * a0.y);
-        // -i c = (c.y, -c.x)
-        U[i][0].x += q * c0.y;
-        U[i][0].y -= q * c0.x;
-        U[i][1].x += q * c1.y;
-        U[i][1].y -= q * c1.x;
-        U[i][2].x += q * c2.y;
-        U[i][2].y -= q * c2.x;
-      }
-    }
-    e[0] = U[0][0];
-    e[1] = U[1][1];
-    e[2] = U[2][2];
-    e[3] = make_double2(0.5 * (U[1][2].x + U[2][1].x), 0.5 * (U[1][2].y + U[2][1].y));
-    e[4] = make_double2(0.5 * (U[0][2].x + U[2][0].x), 0.5 * (U[0][2].y + U[2][0].y));
-    e[5] = make_double2(0.5 * (U[0][1].x + U[1][0].x), 0.5 * (U[0][1].y + U[1][0].y));
-    if (C.frm)
-      green_bin_rot(e, kx, ky, kz, n, C);
-    else
-      green_bin(e, kx, ky, kz, n, C);
+  for (int a = 0; a < 3; ++a) {
+    const int up = (t >> a) & 1;
+    v[a] = q.f[a] + up;
+    v[a] -= v[a] >= n ? n : 0;
+    w *= up ? q.fr[a] : 1.0 - q.fr[a];
   }
+  if (w == 0.0) return;
+  const int64_t id = ((int64_t)v[2] * n + v[1]) * n + v[0];
+  const int32_t prev = atomicCAS(&map[id], -1, t);
+  unsigned long long* rec = reinterpret_cast<unsigned long long*>(sums + (size_t)(prev == -1 ? t : prev) * 18);
+#pragma unroll
+  for (int c = 0; c < 9; ++c) {
+    const int64_t f = llrint(w * q.M[c] * scale);
+    atomicAdd(&rec[2 * c], (unsigned long long)(f >> 32));
+    atomicAdd(&rec[2 * c + 1], (unsigned long long)(uint32_t)f);
+  }
+}
+
+// The records as doubles, twelve per record (the last three zero).
+__global__ __launch_bounds__(256) void k_piece_values(const int64_t* __restrict__ sums, int nrec, double inv,
+                                                      double* __restrict__ vals) {
+  const int t = blockIdx.x * 256 + threadIdx.x;
+  if (t >= 12 * nrec) return;
+  const int r = t / 12, c = t % 12;
+  const int64_t* s = sums + (size_t)r * 18 + 2 * c;
+  vals[t] = c < 9 ? ((double)s[0] * 0x1p32 + (double)s[1]) * inv : 0.0;
+}
+
+// One thread per bin: the nine transformed components (six in a, three in b)
+// to the stress spectrum.
+template <typename S>
+__global__ __launch_bounds__(256) void k_path_bins(const double2* __restrict__ a, const double2* __restrict__ b, int n,
+                                                   int Pd, int P, double L, Cubic C,
+                                                   typename Cplx<S>::T* __restrict__ spec) {
+  const int NH = n / 2 + 1;
+  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (t >= (int64_t)n * n * NH) return;
+  const int kx = (int)(t % NH);
+  const int64_t r = t / NH;
+  const int ky = (int)(r % n), kz = (int)(r / n);
+  const size_t o = spec_at(kz, ky, kx, 0, n, Pd);
+  double2 al[9], e[6];
+#pragma unroll
+  for (int c = 0; c < 6; ++c) al[c] = a[o + c];
+#pragma unroll
+  for (int c = 0; c < 3; ++c) al[6 + c] = b[o + c];
+  path_bin(al, kx, ky, kz, n, L, C, e);
   typename Cplx<S>::T* const out = spec + spec_at(kz, ky, kx, 0, n, P);
 #pragma unroll
   for (int c = 0; c < 6; ++c) st2(out + c, e[c]);
@@ -1858,6 +1988,38 @@ hipError_t launch_path_spectrum(bool fp64, const DevPiece* pieces, int np, SpecG
                        (double2*)spec);
   else
     hipLaunchKernelGGL(k_path_spectrum<float>, dim3(grid), dim3(256), 0, s, pieces, np, g.n, g.P, L, C, tw,
+                       (float2*)spec);
+  return hipGetLastError();
+}
+
+hipError_t launch_path_points(bool fp64, const DevPiece* pieces, int np, double scale, SpecGeom g, double L, Cubic C,
+                              const double2* tw, char* scratch, void* spec, hipStream_t s) {
+  const PathScratch o = path_scratch(g.n, np);
+  const SpecGeom gd{g.n, spec_pitch(g.n, true)};
+  double2* const sp[2] = {(double2*)(scratch + o.a), (double2*)(scratch + o.b)};
+  int32_t* const map = (int32_t*)(scratch + o.map);
+  int64_t* const sums = (int64_t*)(scratch + o.sums);
+  double* const vals = (double*)(scratch + o.vals);
+  const int nrec = 8 * np;
+  hipError_t e = launch_fill_i32(map, (int64_t)g.n * g.n * g.n, -1, s);
+  if (e == hipSuccess) e = launch_fill_i32((int32_t*)sums, (int64_t)nrec * 36, 0, s);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_piece_points, dim3((nrec + 255) / 256), dim3(256), 0, s, pieces, np, g.n, scale, map, sums);
+  hipLaunchKernelGGL(k_piece_values, dim3((12 * nrec + 255) / 256), dim3(256), 0, s, sums, nrec, 1.0 / scale, vals);
+  const Prune full{0, g.n, 0, g.n};
+  for (int h = 0; h < 2; ++h) {
+    if ((e = launch_x_forward_points(map, vals + 6 * h, 12, sp[h], gd, tw, s)) != hipSuccess ||
+        (e = launch_pencil(true, false, 1, sp[h], gd, full, tw, nullptr, s)) != hipSuccess ||
+        (e = launch_pencil(true, false, 2, sp[h], gd, full, tw, nullptr, s)) != hipSuccess)
+      return e;
+  }
+  const int64_t bins = (int64_t)g.n * g.n * (g.n / 2 + 1);
+  const int grid = (int)((bins + 255) / 256);
+  if (fp64)
+    hipLaunchKernelGGL(k_path_bins<double>, dim3(grid), dim3(256), 0, s, sp[0], sp[1], g.n, gd.P, g.P, L, C,
+                       (double2*)spec);
+  else
+    hipLaunchKernelGGL(k_path_bins<float>, dim3(grid), dim3(256), 0, s, sp[0], sp[1], g.n, gd.P, g.P, L, C,
                        (float2*)spec);
   return hipGetLastError();
 }
