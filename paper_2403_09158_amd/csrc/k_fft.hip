@@ -901,15 +901,16 @@ struct FusedPlan {
 };
 
 // Two-column tiles without the operand prefetch and register twiddles (which
-// would take their registers) for the even lengths 64 .. 256: three or more
+// would take their registers) for the lengths 24 .. 256: three or more
 // resident workgroups per CU hide more latency than one four-column one with
 // the prefetch (FP32 pass at 256^3 0.33 -> 0.27 ms, 240^3 0.33 -> 0.27, 160^3
-// 0.098 -> 0.077, 128^3 0.070 -> 0.042, 64^3 0.030 -> 0.013).  At 512 the
+// 0.098 -> 0.077, 128^3 0.070 -> 0.042, 64^3 0.030 -> 0.013, 48^3 0.024 ->
+// 0.014, 32^3 0.013 -> 0.008).  At 512 the
 // two-column tile keeps the prefetch (without it 3.6 -> 4.2 ms), and the odd
 // 129 keeps four columns (two: 0.83 -> 1.03 ms per solve).
 template <int N>
 constexpr bool zg_narrow() {
-  return N >= 64 && N <= 256 && !has_direct(plan_fused(N));
+  return N >= 24 && N <= 256 && !has_direct(plan_fused(N));
 }
 
 // columns per tile: four, or two for the lengths above, at N = 512 (where a
@@ -1302,6 +1303,20 @@ int tile_grid(K kernel, int threads, int ntiles, bool prefetch) {
   return std::max(8, (g / 8) * 8);
 }
 
+// Grid of a kernel that prefetches its next tile, and whether it walks tiles
+// claimed from counters: as many workgroups as stay resident, where each then
+// has several tiles to walk; else one workgroup per tile (no counters), since
+// claiming two tiles ahead leaves part of the chip idle.  Both y passes of a
+// solve, us with / without walking, and tiles per resident workgroup: 64^3 51 /
+// 18 (1), 96^3 95 / 27 (2), 128^3 119 / 42 (6), 160^3 125 / 72 (7), 240^3 291 / 357
+// (29), 256^3 306 / 374 (33).
+template <class K>
+int walk_grid(K kernel, int threads, int ntiles, bool& walk) {
+  const int g = tile_grid(kernel, threads, ntiles, true);
+  walk = ntiles >= 16 * g;
+  return g < 0 || walk ? g : ((ntiles + 7) / 8) * 8;
+}
+
 template <int N, typename S>
 hipError_t go_xf(const int32_t* own, const int2* lnk, const DevDefect* defs, int ndef, const double* dense,
                  void* spec, SpecGeom g, const double2* tw, uint32_t* zero_ctr, hipStream_t s) {
@@ -1373,9 +1388,11 @@ hipError_t go_pencil(bool inv, int axis, void* spec, SpecGeom g, Prune pr, const
   auto* k = axis == 1 ? (inv ? (prune ? k_pencil<N, S, true, LT, true, 1> : k_pencil<N, S, true, LT, false, 1>)
                              : (prune ? k_pencil<N, S, false, LT, true, 1> : k_pencil<N, S, false, LT, false, 1>))
                       : (inv ? k_pencil<N, S, true, LT, false, 2> : k_pencil<N, S, false, LT, false, 2>);
-  const int grid = tile_grid(k, T, ntiles, pencil_pipe<N, S>());
+  bool walk = false;
+  const int grid = pencil_pipe<N, S>() ? walk_grid(k, T, ntiles, walk) : tile_grid(k, T, ntiles, false);
   if (grid < 0) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k, dim3(grid), dim3(T), 0, s, (C2*)spec, pr, tw, ntiles, ctr, (const HopJob*)nullptr, 0);
+  hipLaunchKernelGGL(k, dim3(grid), dim3(T), 0, s, (C2*)spec, pr, tw, ntiles, walk ? ctr : nullptr,
+                     (const HopJob*)nullptr, 0);
   return hipGetLastError();
 }
 
@@ -1436,25 +1453,30 @@ hipError_t go_hop_batch(const HopJob* jobs, int njob, SpecGeom g, Cubic C, const
   constexpr int KB = (N / 2 + 1 + pencil_wx<N, LT>() - 1) / pencil_wx<N, LT>();
   const Prune none{0, N, 0, N};
   {
+    // the tiles of the jobs' pruned planes, few per resident workgroup, in a
+    // fixed order
     auto* k = k_pencil<N, S, false, LT, true, 1, true>;
-    const int grid = pipe ? tile_grid(k, TP, njob * N * KB, true) : ((njob * N * KB + 7) / 8) * 8;
+    const int grid = tile_grid(k, TP, njob * N * KB, pipe);
     if (grid < 0) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k, dim3(grid), dim3(TP), 0, s, (C2*)nullptr, none, tw, 0, ctr, jobs, njob);
+    hipLaunchKernelGGL(k, dim3(grid), dim3(TP), 0, s, (C2*)nullptr, none, tw, 0, (uint32_t*)nullptr, jobs, njob);
   }
   {
     constexpr int W = zg_width<N, S>();
     constexpr int T = zg_threads<N, S>();
     constexpr int NT = N * ((N / 2 + 1 + W - 1) / W);
     auto* k = C.frm ? k_zgreen<N, S, true, true, true> : k_zgreen<N, S, true, false, true>;
-    const int grid = tile_grid(k, T, njob * NT, zpipe);
+    bool walk = false;
+    const int grid = zpipe ? walk_grid(k, T, njob * NT, walk) : tile_grid(k, T, njob * NT, false);
     if (grid < 0) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k, dim3(grid), dim3(T), 0, s, (C2*)nullptr, C, none, tw, ctr + 8, jobs, njob);
+    hipLaunchKernelGGL(k, dim3(grid), dim3(T), 0, s, (C2*)nullptr, C, none, tw, walk ? ctr + 8 : nullptr, jobs, njob);
   }
   {
     auto* k = k_pencil<N, S, true, LT, false, 1, true>;
-    const int grid = tile_grid(k, TP, njob * N * KB, pipe);
+    bool walk = false;
+    const int grid = pipe ? walk_grid(k, TP, njob * N * KB, walk) : tile_grid(k, TP, njob * N * KB, false);
     if (grid < 0) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k, dim3(grid), dim3(TP), 0, s, (C2*)nullptr, none, tw, 0, ctr + 16, jobs, njob);
+    hipLaunchKernelGGL(k, dim3(grid), dim3(TP), 0, s, (C2*)nullptr, none, tw, 0, walk ? ctr + 16 : nullptr, jobs,
+                       njob);
   }
   // accumulating x inverse (a hop's mean-stress change is zero)
   hipLaunchKernelGGL((k_x_inverse<N, S, true, false, true>), dim3(njob * N * (N / x_rows(N))), dim3(TX), 0, s,
@@ -1588,9 +1610,11 @@ hipError_t go_zgreen(void* spec, SpecGeom g, Cubic C, Prune pr, const double2* t
   if (g.P != spec_pitch(N, sizeof(S) == 8)) return hipErrorInvalidValue;
   auto* k = C.frm ? (prune ? k_zgreen<N, S, true, true> : k_zgreen<N, S, false, true>)
                   : (prune ? k_zgreen<N, S, true, false> : k_zgreen<N, S, false, false>);
-  const int grid = tile_grid(k, T, NT, zg_pipe<N, S>());
+  bool walk = false;
+  const int grid = zg_pipe<N, S>() ? walk_grid(k, T, NT, walk) : tile_grid(k, T, NT, false);
   if (grid < 0) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k, dim3(grid), dim3(T), 0, s, (C2*)spec, C, pr, tw, ctr, (const HopJob*)nullptr, 0);
+  hipLaunchKernelGGL(k, dim3(grid), dim3(T), 0, s, (C2*)spec, C, pr, tw, walk ? ctr : nullptr, (const HopJob*)nullptr,
+                     0);
   return hipGetLastError();
 }
 
