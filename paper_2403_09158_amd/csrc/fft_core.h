@@ -251,8 +251,10 @@ struct Dft<15, INV> {
 //   C_k = x_0 + sum_j a_j cos(2 pi j k / R),  S_k = sum_j b_j sin(2 pi j k / R),
 // with the cosines and sines read from the length-N twiddle table
 // (W_N^{m N / R} = cos - i sin of 2 pi m / R).
+// Outputs are shared out over `parts` threads that hold the same inputs: this
+// one forms the pairs k of part `part`, and part 0 also X_0.
 template <int N, int R, bool INV, class Put>
-__device__ __forceinline__ void dft_direct(double2* v, const double2* tw, Put&& put) {
+__device__ __forceinline__ void dft_direct(double2* v, const double2* tw, int part, int parts, Put&& put) {
   static_assert(R % 2 == 1 && N % R == 0, "odd radix dividing N");
   constexpr int H = (R - 1) / 2;
   double2 x0 = v[0], sum = v[0];
@@ -263,9 +265,9 @@ __device__ __forceinline__ void dft_direct(double2* v, const double2* tw, Put&& 
     v[R - j] = b;
     sum = cadd(sum, a);
   }
-  put(0, sum);
+  if (part == 0) put(0, sum);
 #pragma unroll 1
-  for (int k = 1; k <= H; ++k) {
+  for (int k = 1 + H * part / parts; k <= H * (part + 1) / parts; ++k) {
     double2 C = x0, S = make_double2(0.0, 0.0);
     int m = 0;
 #pragma unroll
@@ -315,6 +317,14 @@ __device__ __forceinline__ double2 twiddle(const TwReg<R>& t, int r, int) {
   return INV ? conjd(t.w[r]) : t.w[r];
 }
 
+// Threads per butterfly of a direct radix: its outputs cost a product each with
+// every input, and a stage of a large radix has few butterflies, so the
+// workgroup's threads share them out (up to seven each, three output pairs of a
+// length-43 butterfly per thread) instead of leaving most threads idle (x inverse
+// pass: 27 butterflies for 256 threads).  129^3 solves, us before / now: FP32 762
+// / 559, FP64 849 / 523.
+constexpr int direct_split(int nb, int threads) { return nb >= threads ? 1 : (threads / nb < 7 ? threads / nb : 7); }
+
 // One Stockham stage over `nfft` transforms of length N with radix R after
 // Ns = product of earlier radices.  Butterfly b -> (transform f, index j) by
 // MAP (pencil: f fastest across lanes, so columns stay contiguous; row: j
@@ -349,6 +359,35 @@ __device__ __forceinline__ void stage(const TW& tw, Load&& load, Store&& store, 
   constexpr int NB = NFFT * (N / R);
   constexpr int BPT = (NB + T - 1) / T;
   static_assert(!is_twreg<TW>::value || NB <= T, "register twiddles need at most one butterfly per thread");
+  if constexpr (direct_radix(R) && direct_split(NB, T) > 1) {
+    constexpr int PARTS = direct_split(NB, T);
+    double2 v[R];
+    const int b = tid % NB, part = tid / NB;
+    int f, j;
+    bfly_index<M, N, R, NFFT, GW>(b, f, j);
+    if (part < PARTS) {
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        if constexpr (std::is_invocable_v<Load, int, int, int>)
+          v[r] = load(f, j + r * (N / R), r);
+        else
+          v[r] = load(f, j + r * (N / R));
+      }
+    }
+    if (sync_between) __syncthreads();
+    if (part < PARTS) {
+      const int k = j % NS;
+      if (NS > 1) {
+#pragma unroll
+        for (int r = 1; r < R; ++r) v[r] = cmul(v[r], twiddle<INV>(tw, r, k * r * (N / (NS * R))));
+      }
+      const int base = (j / NS) * NS * R + k;
+      static_assert(!is_twreg<TW>::value, "a direct radix reads the twiddle table");
+      static_assert(!std::is_invocable_v<Store, int, int, double2, int>, "no slot-indexed store after a direct radix");
+      dft_direct<N, R, INV>(v, tw, part, PARTS, [&](int r, double2 x) { store(f, base + r * NS, x); });
+    }
+    return;
+  }
   double2 v[BPT][R];
 #pragma unroll
   for (int q = 0; q < BPT; ++q) {
@@ -385,7 +424,7 @@ __device__ __forceinline__ void stage(const TW& tw, Load&& load, Store&& store, 
         // compile-time slot cannot follow a direct radix
         static_assert(!is_twreg<TW>::value, "a direct radix reads the twiddle table");
         static_assert(!std::is_invocable_v<Store, int, int, double2, int>, "no slot-indexed store after a direct radix");
-        dft_direct<N, R, INV>(v[q], tw, [&](int r, double2 x) { store(f, base + r * NS, x); });
+        dft_direct<N, R, INV>(v[q], tw, 0, 1, [&](int r, double2 x) { store(f, base + r * NS, x); });
       } else {
         Dft<R, INV>::run(v[q]);
 #pragma unroll

@@ -24,6 +24,15 @@ constexpr int max_nb(int N, int F) {
   }
   return m;
 }
+// Wavefronts per SIMD to leave registers for: two with a direct radix, whose
+// butterfly holds 43 operands (else the compiler takes more than half of them;
+// 129^3 FP32 z pass 177 -> 150 us, both y passes 178 -> 158, x inverse 77 -> 52).
+// The x forward and the accumulating or FP64 x inverse passes lose more to
+// spilled operands than they gain (FP32 x forward 97 -> 143).
+template <int N>
+constexpr int min_waves() {
+  return has_direct(plan_of(N)) ? 2 : 1;
+}
 constexpr int pick_T(int nb) { return nb >= 256 ? 256 : ((nb + 63) / 64) * 64; }
 
 
@@ -695,19 +704,15 @@ constexpr int pencil_rmax() {
 template <int N, typename LT>
 constexpr int pencil_wx() {
   constexpr int w = sizeof(LT) == 8 ? 4 : 2;
-  return N >= 512 ? w / 2 : w;
+  return N >= 512 ? w / 2 : (has_direct(plan_of(N)) ? 2 : w);
 }
 
 // Threads of a tile pass over NF transforms: one butterfly per thread in the
-// widest-radix stage.  With a direct radix that stage has few butterflies, so
-// the size is set by the other stages instead: the least multiple of NF that
-// fills whole wavefronts.
+// widest-radix stage.  A direct radix has few butterflies and shares each out
+// over seven threads (direct_split).
 template <int N>
 constexpr int tile_threads(int NF, int rmax) {
-  if (!has_direct(plan_of(N)) && !has_direct(plan_fused(N))) return NF * (N / rmax);
-  int t = NF;
-  while (t % 64) t += NF;
-  return t;
+  return (has_direct(plan_of(N)) || has_direct(plan_fused(N)) ? 7 : 1) * NF * (N / rmax);
 }
 
 template <int N, typename LT>
@@ -736,7 +741,8 @@ __device__ __forceinline__ int job_of_tile(int t, int njob, Count&& cnt, int& lo
 // spectrum and (y pass, PRUNE) its planes and input rows come from its record;
 // spec, pr and ntiles are then unused.
 template <int N, typename S, bool INV, typename LT, bool PRUNE, int AXIS, bool BATCH = false>
-__global__ __launch_bounds__((pencil_threads<N, LT>())) void k_pencil(typename Cplx<S>::T* __restrict__ spec,
+__global__ __launch_bounds__((pencil_threads<N, LT>())) __attribute__((amdgpu_waves_per_eu(min_waves<N>()))) void
+k_pencil(typename Cplx<S>::T* __restrict__ spec,
                                                                      Prune pr, const double2* __restrict__ twg,
                                                                      int ntiles, uint32_t* __restrict__ ctr,
                                                                      const HopJob* __restrict__ jobs = nullptr,
@@ -906,8 +912,9 @@ struct FusedPlan {
 // the prefetch (FP32 pass at 256^3 0.33 -> 0.27 ms, 240^3 0.33 -> 0.27, 160^3
 // 0.098 -> 0.077, 128^3 0.070 -> 0.042, 64^3 0.030 -> 0.013, 48^3 0.024 ->
 // 0.014, 32^3 0.013 -> 0.008).  At 512 the
-// two-column tile keeps the prefetch (without it 3.6 -> 4.2 ms), and the odd
-// 129 keeps four columns (two: 0.83 -> 1.03 ms per solve).
+// two-column tile keeps the prefetch (without it 3.6 -> 4.2 ms).  The odd 129
+// takes two columns as well, 252 threads (its length-43 butterflies shared out
+// over seven threads each; 129^3 FP32 pass 0.274 -> 0.150 ms).
 template <int N>
 constexpr bool zg_narrow() {
   return N >= 24 && N <= 256 && !has_direct(plan_fused(N));
@@ -917,7 +924,7 @@ constexpr bool zg_narrow() {
 // four-column tile would not fit) and with FP64 storage from N = 256 on
 template <int N, typename S>
 constexpr int zg_width() {
-  return (N >= 512 || zg_narrow<N>() || (sizeof(S) == 8 && N >= 256)) ? 2 : 4;
+  return (N >= 512 || zg_narrow<N>() || has_direct(plan_fused(N)) || (sizeof(S) == 8 && N >= 256)) ? 2 : 4;
 }
 
 // one butterfly per thread in the widest-radix stage; a multiple of the 6 W
@@ -951,7 +958,7 @@ constexpr bool zg_pipe() {
 // wavefronts per CU), else one (no bound beyond the workgroup size).
 template <int N, typename S>
 constexpr int zg_waves_per_eu() {
-  return zg_narrow<N>() ? 3 : 1;
+  return zg_narrow<N>() ? 3 : min_waves<N>();
 }
 
 // LDS row swizzle: the low three bits of the z index are XORed with the next
@@ -1170,7 +1177,8 @@ __global__ __launch_bounds__(256) void k_green(typename Cplx<S>::T* __restrict__
 // SWAP (with ACC): the stress replaces the one in sig, and the total it is part
 // of is renewed with it, total = (total - old) + new.
 template <int N, typename S, bool ACC, bool BG, bool BATCH = false, bool MASK = false, bool SWAP = false>
-__global__ __launch_bounds__(pick_T(max_nb(N, 3 * x_rows(N)))) void k_x_inverse(
+__global__ __launch_bounds__(pick_T(max_nb(N, 3 * x_rows(N))))
+__attribute__((amdgpu_waves_per_eu(sizeof(S) == 4 && !ACC ? min_waves<N>() : 1))) void k_x_inverse(
     const typename Cplx<S>::T* __restrict__ spec, double* __restrict__ sig, const double* __restrict__ mean6,
     const double2* __restrict__ twg, const double* __restrict__ bg, int bg_mask,
     const HopJob* __restrict__ jobs = nullptr, const double* add3 = nullptr,
