@@ -364,7 +364,6 @@ struct ec_state {
   // update scratch
   int32_t* upd_ids = nullptr;
   int64_t upd_cap = 0;
-  double* updE = nullptr;     // 12 doubles: the old and the new eigenstrain of a moved defect
   uint32_t* tilectr = nullptr;  // NTILECTR tile counters of the persistent passes
   // jump probes: energy changes of the last ec_jump_energies call (jn per
   // defect) and their scratch
@@ -1295,6 +1294,15 @@ ec_status copy_out(void* dst, const void* src, size_t bytes, bool on_device, hip
   return EC_OK;
 }
 
+// Polls an event.
+ec_status wait_event(hipEvent_t ev) {
+  hipError_t q;
+  while ((q = hipEventQuery(ev)) == hipErrorNotReady) {
+  }
+  HIPCHK(q);
+  return EC_OK;
+}
+
 // A per-defect output: to the host through the state's pinned bounce buffer (a
 // direct copy into pageable memory is staged by the runtime), synchronously.
 // Small results returned to a waiting host caller: copied into pinned memory
@@ -1308,10 +1316,7 @@ ec_status copy_small(ec_state* st, void* dst, const void* src, size_t bytes, boo
   if (r != EC_OK) return r;
   HIPCHK(hipMemcpyAsync(hp, src, bytes, hipMemcpyDeviceToHost, s));
   HIPCHK(hipEventRecord(st->pin_out.ev, s));
-  hipError_t q;
-  while ((q = hipEventQuery(st->pin_out.ev)) == hipErrorNotReady) {
-  }
-  HIPCHK(q);
+  if ((r = wait_event(st->pin_out.ev)) != EC_OK) return r;
   std::memcpy(dst, hp, bytes);
   return EC_OK;
 }
@@ -1693,24 +1698,15 @@ ec_status update_q(ec_state* st, int32_t idx, DevDefect nd, hipStream_t s) {
     neg_C_dot(st, m, dadd);
   }
   // --- commit
-  // [old E 48][new E 48][dadd 48][count 8][record]: the eigenstrain change is
-  // -E_old on the old footprint and +E_new on the new one; both as the
-  // rasterised field holds them (the fixed-point components, in the cube
-  // frame of a rotated crystal, where the sparse transform works)
-  char* up = nullptr;
-  if ((r = pin_begin(st->pin_upd, 152 + sizeof(DevDefect), &up)) != EC_OK) return r;
-  {
-    double eo[6], en[6];
-    for (int a = 0; a < 6; ++a) {
-      eo[a] = (double)od.efix[a] * FIX_INV;
-      en[a] = (double)nd.efix[a] * FIX_INV;
-    }
-    std::memcpy(up, eo, 48);
-    std::memcpy(up + 48, en, 48);
+  // the eigenstrain change is -E_old on the old footprint and +E_new on the new
+  // one, both as the rasterised field holds them (the fixed-point components, in
+  // the cube frame of a rotated crystal, where the sparse transform works); it
+  // and the new record go to the kernels by value
+  MoveStrain E12;
+  for (int a = 0; a < 6; ++a) {
+    E12.v[a] = (double)od.efix[a] * FIX_INV;
+    E12.v[6 + a] = (double)nd.efix[a] * FIX_INV;
   }
-  std::memcpy(up + 96, dadd, 48);
-  std::memcpy(up + 144, &cnt_new, 4);
-  std::memcpy(up + 152, &nd, sizeof nd);
   if (!hop && cnt_new > 0) {
     char* ip = nullptr;
     if ((r = pin_begin(st->pin_ids, (size_t)cnt_new * 4, &ip)) != EC_OK) return r;
@@ -1718,17 +1714,24 @@ ec_status update_q(ec_state* st, int32_t idx, DevDefect nd, hipStream_t s) {
     HIPCHK(hipMemcpyAsync(st->upd_ids, ip, (size_t)cnt_new * 4, hipMemcpyHostToDevice, s));
     if ((r = pin_end(st->pin_ids, s)) != EC_OK) return r;
   }
-  HIPCHK(hipMemcpyAsync(st->updE, up, 96, hipMemcpyHostToDevice, s));
-  HIPCHK(hipMemcpyAsync(st->add6 + 12, up + 96, 48, hipMemcpyHostToDevice, s));
+  const double* dmean = st->add6 + 6;  // zeros: a translation leaves the mean
+  if (!hop) {
+    char* up = nullptr;
+    if ((r = pin_begin(st->pin_upd, 48, &up)) != EC_OK) return r;
+    std::memcpy(up, dadd, 48);
+    HIPCHK(hipMemcpyAsync(st->add6 + 12, up, 48, hipMemcpyHostToDevice, s));
+    if ((r = pin_end(st->pin_upd, s)) != EC_OK) return r;
+    dmean = st->add6 + 12;
+  }
   const int32_t* oids = b.ids + od.slot;
-  const int32_t* ocnt = b.cnt + idx;
+  int32_t* const ocnt = b.cnt + idx;
   const int32_t* nids = hop ? nullptr : st->upd_ids;
   {
     const bool fp64 = st->fp64;
     const double sb = spec_valid_bytes(st, fp64), fb = 48.0 * (double)st->n3;
     const double frac_z = (double)zlen / n;
     LAUNCH(st, s, PF_XF, frac_z * ylen / n * sb,
-           launch_x_forward_sparse(fp64, oids, ocnt, nids, cnt_new, sh[0], sh[1], sh[2], st->updE, st->spec, st->g,
+           launch_x_forward_sparse(fp64, oids, ocnt, nids, cnt_new, sh[0], sh[1], sh[2], E12, st->spec, st->g,
                                    ylo, ylen, zlo, zlen, st->tw, st->tilectr, s));
     const Prune py{ylo, ylen, zlo, zlen};
     LAUNCH(st, s, PF_Y, 2 * frac_z * sb, launch_pencil(fp64, false, 1, st->spec, st->g, py, st->tw, st->tilectr, s));
@@ -1738,15 +1741,14 @@ ec_status update_q(ec_state* st, int32_t idx, DevDefect nd, hipStream_t s) {
            launch_z_green(fp64, st->spec, st->g, st->C, pz, st->tw, st->tilectr + 8, s));
     LAUNCH(st, s, PF_Y, 2 * sb, launch_pencil(fp64, true, 1, st->spec, st->g, full, st->tw, st->tilectr + 16, s));
     LAUNCH(st, s, PF_XI, sb + 2 * fb,
-           launch_x_inverse(fp64, true, st->spec, st->sig, st->g, st->add6 + 12, st->tw, s));
+           launch_x_inverse(fp64, true, st->spec, st->sig, st->g, dmean, st->tw, s));
   }
   // membership lists and footprint ids of the moved defect (after the sparse
   // forward pass, which still reads the old footprint)
   LAUNCH(st, s, PF_RASTER, 0,
-         launch_move_lists(idx, st->ndef, ocnt, od.slot, nids, cnt_new, nd.slot, sh[0], sh[1], sh[2], n, b.ids, b.lnk,
-                           st->own, s));
+         launch_move_lists(idx, st->ndef, b.cnt, od.slot, nids, cnt_new, sh[0], sh[1], sh[2], n, b.ids, b.lnk, st->own,
+                           b.tab, nd, s));
   if (!hop) {
-    HIPCHK(hipMemcpyAsync(b.cnt + idx, up + 144, 4, hipMemcpyHostToDevice, s));
     if (nd.slot != od.slot) {
       st->ids_used += cap_new;
       st->hcap[idx] = cap_new;
@@ -1755,8 +1757,6 @@ ec_status update_q(ec_state* st, int32_t idx, DevDefect nd, hipStream_t s) {
     st->B_valid = false;
     if (st->classes.size() != ncls_before) st->gcls_ncls = -1;
   }
-  HIPCHK(hipMemcpyAsync(b.tab + idx, up + 152, sizeof nd, hipMemcpyHostToDevice, s));
-  if ((r = pin_end(st->pin_upd, s)) != EC_OK) return r;
   st->hdefs[idx] = nd;
   return EC_OK;
 }
@@ -1991,7 +1991,7 @@ ec_status ec_state_create(ec_ctx* c, const ec_problem* p, ec_state** out) {
     delete st;
     return fail(EC_ERR_DEVICE, "twiddle table allocation failed");
   }
-  void *sp = nullptr, *own = nullptr, *sg = nullptr, *ad = nullptr, *dirs = nullptr, *ue = nullptr, *ri = nullptr;
+  void *sp = nullptr, *own = nullptr, *sg = nullptr, *ad = nullptr, *dirs = nullptr, *ri = nullptr;
   void* tc = nullptr;
   void* fm = nullptr;
   const size_t ob = (size_t)st->n3 * 4;
@@ -2002,14 +2002,13 @@ ec_status ec_state_create(ec_ctx* c, const ec_problem* p, ec_state** out) {
     ledger_free(c, sg, fb);
     ledger_free(c, ad, 256);
     ledger_free(c, dirs, MAXCLS * 48);
-    ledger_free(c, ue, 128);
     ledger_free(c, ri, MAXRUN * sizeof(int4));
     ledger_free(c, tc, 128);
     ledger_free(c, fm, FRAME_LEN * 8);
   };
   if ((r = ledger_alloc(c, st->spec_bytes, &sp)) != EC_OK || (r = ledger_alloc(c, ob, &own)) != EC_OK ||
       (r = ledger_alloc(c, fb, &sg)) != EC_OK || (r = ledger_alloc(c, 256, &ad)) != EC_OK ||
-      (r = ledger_alloc(c, MAXCLS * 48, &dirs)) != EC_OK || (r = ledger_alloc(c, 128, &ue)) != EC_OK ||
+      (r = ledger_alloc(c, MAXCLS * 48, &dirs)) != EC_OK ||
       (r = ledger_alloc(c, 128, &tc)) != EC_OK || (r = ledger_alloc(c, MAXRUN * sizeof(int4), &ri)) != EC_OK ||
       (rotated && (r = ledger_alloc(c, FRAME_LEN * 8, &fm)) != EC_OK)) {
     undo();
@@ -2021,12 +2020,11 @@ ec_status ec_state_create(ec_ctx* c, const ec_problem* p, ec_state** out) {
   st->sig = (double*)sg;
   st->add6 = (double*)ad;
   st->dirs = (double*)dirs;
-  st->updE = (double*)ue;
   st->runinfo = (int4*)ri;
   st->tilectr = (uint32_t*)tc;
   st->frm = (double*)fm;
   st->C.frm = st->frm;
-  st->held = st->spec_bytes + fb + ob + 256 + MAXCLS * 48 + 128 + 128 + MAXRUN * sizeof(int4) +
+  st->held = st->spec_bytes + fb + ob + 256 + MAXCLS * 48 + 128 + MAXRUN * sizeof(int4) +
              (rotated ? FRAME_LEN * 8 : 0);
   hipError_t e = launch_fill_i32(st->own, st->n3, -1, nullptr);
   if (e == hipSuccess) e = hipMemset(st->sig, 0, fb);
@@ -2052,7 +2050,6 @@ void ec_state_destroy(ec_state* st) {
   ledger_free(c, st->sig, fb);
   ledger_free(c, st->add6, 256);
   ledger_free(c, st->dirs, MAXCLS * 48);
-  ledger_free(c, st->updE, 128);
   ledger_free(c, st->tilectr, 128);
   for (auto& b : st->db) {
     ledger_free(c, b.tab, b.cap * sizeof(DevDefect));
@@ -2160,9 +2157,18 @@ ec_status ec_interaction_energies(ec_state* st, void* stream, double* E_out, int
   if (!st->B_valid && (r = compute_self_terms(st, s)) != EC_OK) return r;
   if ((r = join_self(st, s)) != EC_OK) return r;
   const DefBuf& b = st->db[st->cur];
+  // host output: the reduction writes its second copy straight into the pinned
+  // bounce buffer, with no copy behind it
+  const bool to_host = E_out && !on_device && st->ndef > 0;
+  char* hp = nullptr;
+  if (to_host && (r = pin_begin(st->pin_out, (size_t)st->ndef * 8, &hp)) != EC_OK) return r;
   LAUNCH(st, s, PF_REDUCE, 0,
-         launch_reduce(b.tab, st->ndef, b.cnt, b.ids, st->sig, st->B, st->h3c, st->S6, st->E, s));
-  if (E_out && st->ndef > 0) return copy_small(st, E_out, st->E, (size_t)st->ndef * 8, on_device != 0, s);
+         launch_reduce(b.tab, st->ndef, b.cnt, b.ids, st->sig, st->B, st->h3c, st->S6, st->E,
+                       (double*)hp, s));
+  if (!to_host) return E_out && st->ndef > 0 ? copy_out(E_out, st->E, (size_t)st->ndef * 8, true, s) : EC_OK;
+  HIPCHK(hipEventRecord(st->pin_out.ev, s));
+  if ((r = wait_event(st->pin_out.ev)) != EC_OK) return r;
+  std::memcpy(E_out, hp, (size_t)st->ndef * 8);
   return EC_OK;
 }
 
@@ -2210,7 +2216,7 @@ ec_status ec_interaction_energies_noalloc(ec_state* st, void* stream, double* E_
     st->B_valid = true;
   }
   LAUNCH(st, s, PF_REDUCE, 0,
-         launch_reduce(b.tab, st->ndef, b.cnt, b.ids, st->sig, st->B, st->h3c, st->S6, st->E, s));
+         launch_reduce(b.tab, st->ndef, b.cnt, b.ids, st->sig, st->B, st->h3c, st->S6, st->E, nullptr, s));
   if (st->ndef > 0)
     HIPCHK(hipMemcpyAsync(E_dev, st->E, (size_t)st->ndef * 8, hipMemcpyDeviceToDevice, s));
   return EC_OK;
@@ -2456,7 +2462,7 @@ ec_status ec_jump_energies(ec_state* st, const int32_t* jumps, int32_t njump, vo
                         std::memcmp(st->jx_jumps.data(), jumps, 3 * nu * 4) == 0;
   // S(0): the footprint sums of the energies reduction (which also refreshes E)
   LAUNCH(st, s, PF_REDUCE, 0,
-         launch_reduce(b.tab, nd, b.cnt, b.ids, st->sig, st->B, st->h3c, st->S6, st->E, s));
+         launch_reduce(b.tab, nd, b.cnt, b.ids, st->sig, st->B, st->h3c, st->S6, st->E, nullptr, s));
   LAUNCH(st, s, PF_SELF, 0,
          launch_jump_energies(b.tab, nd, b.cnt, b.ids, st->sig, st->n, st->jjumps, njump, st->S6, st->win->K,
                               st->gcls, st->win->D, st->jwork, (int64_t)st->jwork_cap, st->jwbeg, st->jpartial,
@@ -2875,11 +2881,10 @@ ec_status ec_type_store(ec_state* st, const ec_defect* proto, void* stream, int3
   footprint_ids(d, st->n, ids);
   const int m = (int)ids.size();
   ec_ctx* c = st->ctx;
-  Tmp ti{c}, te{c};
+  Tmp ti{c};
   ec_status r;
-  // [ids][zero count]; E: no old eigenstrain, the prototype's (cell frame) as the new one
+  // [ids][zero count]
   if ((r = ledger_alloc(c, ti.b = (size_t)m * 4 + 64, &ti.p)) != EC_OK) return r;
-  if ((r = ledger_alloc(c, te.b = 96, &te.p)) != EC_OK) return r;
   ec_state::TypeSpec t;
   if ((r = ledger_alloc(c, st->spec_bytes, &t.eps)) != EC_OK) return r;
   if ((r = ledger_alloc(c, st->spec_bytes, &t.sig)) != EC_OK) {
@@ -2893,14 +2898,13 @@ ec_status ec_type_store(ec_state* st, const ec_defect* proto, void* stream, int3
     return rc;
   };
   for (int k = 0; k < 3; ++k) t.X0[k] = proto->c[k];
-  double E12[12] = {0, 0, 0, 0, 0, 0};
-  std::copy(d.E, d.E + 6, E12 + 6);
+  MoveStrain E12{};
+  std::copy(d.E, d.E + 6, E12.v + 6);
   const int32_t zero = 0;
   int32_t* dids = (int32_t*)ti.p;
   int32_t* dzero = (int32_t*)((char*)ti.p + (size_t)m * 4);
   if (hipMemcpy(dzero, &zero, 4, hipMemcpyHostToDevice) != hipSuccess ||
-      (m > 0 && hipMemcpy(dids, ids.data(), (size_t)m * 4, hipMemcpyHostToDevice) != hipSuccess) ||
-      hipMemcpy(te.p, E12, 96, hipMemcpyHostToDevice) != hipSuccess)
+      (m > 0 && hipMemcpy(dids, ids.data(), (size_t)m * 4, hipMemcpyHostToDevice) != hipSuccess))
     return undo(fail(EC_ERR_DEVICE, "upload of the prototype failed"));
   const bool fp64 = st->fp64;
   const int n = st->n;
@@ -2909,7 +2913,7 @@ ec_status ec_type_store(ec_state* st, const ec_defect* proto, void* stream, int3
   // planes and the z pass over the cleared spectrum
   hipError_t e = launch_fill_i32((int32_t*)t.eps, (int64_t)(st->spec_bytes / 4), 0, s);
   if (e == hipSuccess)
-    e = launch_x_forward_sparse(fp64, dids, dzero, dids, m, 0, 0, 0, (const double*)te.p, t.eps, st->g, d.lo[1],
+    e = launch_x_forward_sparse(fp64, dids, dzero, dids, m, 0, 0, 0, E12, t.eps, st->g, d.lo[1],
                                 d.w[1], d.lo[2], d.w[2], st->tw, nullptr, s);
   if (e == hipSuccess) e = launch_pencil(fp64, false, 1, t.eps, st->g, rows, st->tw, nullptr, s);
   if (e == hipSuccess) e = launch_pencil(fp64, false, 2, t.eps, st->g, full, st->tw, nullptr, s);

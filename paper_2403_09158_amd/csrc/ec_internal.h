@@ -366,10 +366,13 @@ hipError_t launch_type_energies(bool fp64, const void* sig, const void* te, cons
                                 double scale, double* E, hipStream_t s);
 // Dense voxel-major FP64 input [n^3][6] (the resident stress).
 hipError_t launch_x_forward_vm(bool fp64, const double* vm, void* spec, SpecGeom g, const double2* tw, hipStream_t s);
-// E: 12 doubles, the old eigenstrain (on old_ids) then the new one (on the new ids).
+// E: the old eigenstrain (on old_ids) then the new one (on the new ids).
+struct MoveStrain {
+  double v[12];
+};
 hipError_t launch_x_forward_sparse(bool fp64, const int32_t* old_ids, const int32_t* old_cnt, const int32_t* new_ids,
                                    int new_cnt,
-                                   int shift_x, int shift_y, int shift_z, const double* E, void* spec, SpecGeom g,
+                                   int shift_x, int shift_y, int shift_z, const MoveStrain& E, void* spec, SpecGeom g,
                                    int y_lo, int y_len, int z_lo, int z_len, const double2* tw, uint32_t* zero_ctr,
                                    hipStream_t s);
 // ctr: eight zeroed tile counters for this launch, or nullptr
@@ -448,18 +451,19 @@ hipError_t launch_unraster(const DevDefect* d, int ndef, const int32_t* counts, 
                            hipStream_t s);
 // One defect moved: unlink its old entries [slot, slot + *cnt_old), then link
 // the new ones (new voxel = old shifted by whole voxels when new_ids ==
-// nullptr, else new_ids[0 .. cnt_new) copied into [new_slot, ...)).
-hipError_t launch_move_lists(int def, int ndef, const int32_t* cnt_old, int64_t old_slot, const int32_t* new_ids,
-                             int cnt_new, int64_t new_slot, int shift_x, int shift_y, int shift_z, int n, int32_t* ids,
-                             int2* lnk, int32_t* own, hipStream_t s);
+// nullptr, else new_ids[0 .. cnt_new) copied into [new_slot, ...)) and write its
+// new record (and, with new_ids, its new count) into the table.
+hipError_t launch_move_lists(int def, int ndef, int32_t* cnt, int64_t old_slot, const int32_t* new_ids, int cnt_new,
+                             int shift_x, int shift_y, int shift_z, int n, int32_t* ids, int2* lnk, int32_t* own,
+                             DevDefect* tab, const DevDefect& rec, hipStream_t s);
 hipError_t launch_fill_i32(int32_t* p, int64_t count, int32_t v, hipStream_t s);
 hipError_t launch_mean_stress(const DevDefect* d, const int32_t* counts, int ndef, int64_t n3, Cubic C, int bc,
                               double* add6, hipStream_t s);
 hipError_t launch_scan(const int32_t* counts, int ndef, int64_t* offsets, hipStream_t s);
 hipError_t launch_fill_i64(int64_t* p, int64_t count, int64_t v, hipStream_t s);
-// sig: the resident stress, voxel-major [n^3][6]
+// sig: the resident stress, voxel-major [n^3][6]; E2: a second copy of E or nullptr
 hipError_t launch_reduce(const DevDefect* d, int ndef, const int32_t* counts, const int32_t* ids, const double* sig,
-                         const double* B, double h3c, double* S6, double* E, hipStream_t s);
+                         const double* B, double h3c, double* S6, double* E, double* E2, hipStream_t s);
 hipError_t launch_window_crop(const double* sig, int n, int D, int b, double* K, hipStream_t s);
 hipError_t launch_class_windows(const double* K, int D, const double* dirs, int ncls, double* g, hipStream_t s);
 // Self-term work item: rows [p0, p1) of defect `def`'s pair triangle.

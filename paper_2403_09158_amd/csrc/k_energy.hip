@@ -103,9 +103,10 @@ __device__ __forceinline__ void reduce_defect(const DevDefect* __restrict__ defs
 __global__ __launch_bounds__(64 * RDW) void k_reduce(const DevDefect* __restrict__ defs, const int32_t* __restrict__ cnt,
                                                      const int32_t* __restrict__ ids, const double* __restrict__ sig,
                                                      const double* __restrict__ B, double h3c,
-                                                     double* __restrict__ S6, double* __restrict__ E, int ndef) {
+                                                     double* __restrict__ S6, double* __restrict__ E,
+                                                     double* __restrict__ E2, int ndef) {
   const int i = blockIdx.x * RDW + (int)(threadIdx.x >> 6);
-  if (i < ndef) reduce_defect(defs, cnt, ids, sig, B, h3c, S6, E, nullptr, i, (int)(threadIdx.x & 63));
+  if (i < ndef) reduce_defect(defs, cnt, ids, sig, B, h3c, S6, E, E2, i, (int)(threadIdx.x & 63));
 }
 
 // Batched hops: the energies of every defect of every job (a fixed grid of
@@ -985,10 +986,10 @@ hipError_t launch_set_class(DevDefect* d, int ndef, const ClassTag* tags, hipStr
 }
 
 hipError_t launch_reduce(const DevDefect* d, int ndef, const int32_t* counts, const int32_t* ids, const double* sig,
-                         const double* B, double h3c, double* S6, double* E, hipStream_t s) {
+                         const double* B, double h3c, double* S6, double* E, double* E2, hipStream_t s) {
   if (ndef == 0) return hipSuccess;
   hipLaunchKernelGGL(k_reduce, dim3((ndef + RDW - 1) / RDW), dim3(64 * RDW), 0, s, d, counts, ids, sig, B, h3c, S6, E,
-                     ndef);
+                     E2, ndef);
   return hipGetLastError();
 }
 

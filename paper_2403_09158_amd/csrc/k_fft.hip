@@ -648,7 +648,7 @@ __device__ __forceinline__ void xfs_block(double2* buf, const double2* tw, const
 template <int N, typename S>
 __global__ __launch_bounds__(pick_T(max_nb(N, 3 * x_rows(N)))) void k_x_forward_sparse(
     const int32_t* __restrict__ old_ids, const int32_t* __restrict__ old_cnt_p, const int32_t* __restrict__ new_ids,
-    int new_cnt, int sx, int sy, int sz, const double* __restrict__ E, typename Cplx<S>::T* __restrict__ spec, int P,
+    int new_cnt, int sx, int sy, int sz, MoveStrain E, typename Cplx<S>::T* __restrict__ spec, int P,
     int y_lo, int y_len, int z_lo, const double2* __restrict__ twg, uint32_t* __restrict__ zero_ctr) {
   constexpr int NF = 3 * x_rows(N);
   constexpr int T = pick_T(max_nb(N, NF));
@@ -657,7 +657,7 @@ __global__ __launch_bounds__(pick_T(max_nb(N, 3 * x_rows(N)))) void k_x_forward_
   __shared__ double2 tw[N];
   if (zero_ctr && blockIdx.x == 0 && threadIdx.x < NTILECTR) zero_ctr[threadIdx.x] = 0u;
   for (int i = threadIdx.x; i < N; i += T) tw[i] = twg[i];
-  xfs_block<N, S>(buf, tw, old_ids, *old_cnt_p, new_ids, new_cnt, sx, sy, sz, E, spec, P, y_lo, y_len, z_lo,
+  xfs_block<N, S>(buf, tw, old_ids, *old_cnt_p, new_ids, new_cnt, sx, sy, sz, E.v, spec, P, y_lo, y_len, z_lo,
                   blockIdx.x);
 }
 
@@ -1367,8 +1367,8 @@ hipError_t go_xf_vm(const double* vm, void* spec, SpecGeom g, const double2* tw,
 }
 
 template <int N, typename S>
-hipError_t go_xfs(const int32_t* oi, const int32_t* oc, const int32_t* ni, int nc, int sx, int sy, int sz, const double* E,
-                  void* spec, SpecGeom g, int ylo, int ylen, int zlo, int zlen, const double2* tw, uint32_t* zero_ctr,
+hipError_t go_xfs(const int32_t* oi, const int32_t* oc, const int32_t* ni, int nc, int sx, int sy, int sz,
+                  const MoveStrain& E, void* spec, SpecGeom g, int ylo, int ylen, int zlo, int zlen, const double2* tw, uint32_t* zero_ctr,
                   hipStream_t s) {
   constexpr int T = pick_T(max_nb(N, 3 * x_rows(N)));
   static_assert(T >= NTILECTR, "the first block zeroes the tile counters");
@@ -1569,7 +1569,7 @@ hipError_t launch_x_forward_vm(bool fp64, const double* vm, void* spec, SpecGeom
 }
 
 hipError_t launch_x_forward_sparse(bool fp64, const int32_t* old_ids, const int32_t* old_cnt, const int32_t* new_ids,
-                                   int new_cnt, int sx, int sy, int sz, const double* E, void* spec, SpecGeom g,
+                                   int new_cnt, int sx, int sy, int sz, const MoveStrain& E, void* spec, SpecGeom g,
                                    int y_lo, int y_len, int z_lo, int z_len, const double2* tw, uint32_t* zero_ctr,
                                    hipStream_t s) {
   switch (g.n) {

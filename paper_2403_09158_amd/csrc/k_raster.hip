@@ -178,15 +178,22 @@ __device__ __forceinline__ int shift_id(int id, int sx, int sy, int sz, int n) {
   return (z * n + y) * n + x;
 }
 
-// Remove defect `def` from the chains of its old voxels.  Each voxel of one
-// footprint is visited by exactly one thread, and no other chain changes
-// meanwhile.  The defect sits on the chain either as a terminal id or as an
-// entry; either way the link that points to it is redirected past it.
-__global__ __launch_bounds__(RT) void k_unlink(int def, int max_links, const int32_t* __restrict__ cnt_p,
-                                               int64_t slot, const int32_t* __restrict__ ids, int2* __restrict__ lnk,
-                                               int32_t* __restrict__ own) {
-  const int cnt = *cnt_p;
-  for (int k = blockIdx.x * RT + threadIdx.x; k < cnt; k += gridDim.x * RT) {
+// A moved defect taken from the chains of its old voxels, then put on those of
+// its new ones (ids shifted in place, or copied from new_ids), and its record
+// renewed.  Each voxel of one footprint is visited by exactly one thread, and no
+// other chain changes meanwhile.  The defect sits on a chain either as a
+// terminal id or as an entry; either way the link that points to it is
+// redirected past it.  One workgroup: a footprint takes a few steps of it, and
+// its barrier orders the two halves, which as two launches of sixteen
+// workgroups took 4.5 us each with the gap between them.
+constexpr int MVT = 1024;
+
+__global__ __launch_bounds__(MVT) void k_move_lists(int def, int max_links, int32_t* __restrict__ cnt_p, int64_t slot,
+                                                    const int32_t* __restrict__ new_ids, int cnt_new, int sx, int sy,
+                                                    int sz, int n, int32_t* ids, int2* lnk, int32_t* own,
+                                                    DevDefect* __restrict__ tab, DevDefect rec) {
+  const int old_cnt = cnt_p[def];
+  for (int k = threadIdx.x; k < old_cnt; k += MVT) {
     int32_t* p = &own[ids[slot + k]];
     for (int guard = 0; guard < max_links; ++guard) {  // a chain holds each defect once
       const int32_t link = *p;
@@ -203,21 +210,20 @@ __global__ __launch_bounds__(RT) void k_unlink(int def, int max_links, const int
       p = &L->y;
     }
   }
-}
-
-// Link the moved defect's new entries (ids shifted in place, or copied from new_ids).
-__global__ __launch_bounds__(RT) void k_link(int def, const int32_t* __restrict__ cnt_p, int64_t old_slot,
-                                             const int32_t* __restrict__ new_ids, int cnt_new, int64_t new_slot,
-                                             int sx, int sy, int sz, int n, int32_t* __restrict__ ids,
-                                             int2* __restrict__ lnk, int32_t* __restrict__ own) {
-  const int cnt = new_ids ? cnt_new : *cnt_p;
-  for (int k = blockIdx.x * RT + threadIdx.x; k < cnt; k += gridDim.x * RT) {
-    const int64_t e = new_slot + k;
-    const int id = new_ids ? new_ids[k] : shift_id(ids[old_slot + k], sx, sy, sz, n);
+  __threadfence();
+  __syncthreads();
+  const int cnt = new_ids ? cnt_new : old_cnt;
+  for (int k = threadIdx.x; k < cnt; k += MVT) {
+    const int64_t e = rec.slot + k;
+    const int id = new_ids ? new_ids[k] : shift_id(ids[slot + k], sx, sy, sz, n);
     ids[e] = id;
     int32_t next = -1;
     if (atomicCAS(&own[id], -1, def) != -1) next = atomicExch(&own[id], entry_link(e));
     lnk[e] = make_int2(def, next);
+  }
+  if (threadIdx.x == 0) {
+    if (new_ids) cnt_p[def] = cnt;
+    tab[def] = rec;
   }
 }
 
@@ -352,14 +358,11 @@ hipError_t launch_unraster(const DevDefect* d, int ndef, const int32_t* counts, 
   return hipGetLastError();
 }
 
-hipError_t launch_move_lists(int def, int ndef, const int32_t* cnt_old, int64_t old_slot, const int32_t* new_ids,
-                             int cnt_new, int64_t new_slot, int sx, int sy, int sz, int n, int32_t* ids, int2* lnk,
-                             int32_t* own, hipStream_t s) {
-  hipLaunchKernelGGL(k_unlink, dim3(16), dim3(RT), 0, s, def, ndef, cnt_old, old_slot, ids, lnk, own);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_link, dim3(16), dim3(RT), 0, s, def, cnt_old, old_slot, new_ids, cnt_new, new_slot, sx, sy, sz,
-                     n, ids, lnk, own);
+hipError_t launch_move_lists(int def, int ndef, int32_t* cnt, int64_t old_slot, const int32_t* new_ids, int cnt_new,
+                             int shift_x, int shift_y, int shift_z, int n, int32_t* ids, int2* lnk, int32_t* own,
+                             DevDefect* tab, const DevDefect& rec, hipStream_t s) {
+  hipLaunchKernelGGL(k_move_lists, dim3(1), dim3(MVT), 0, s, def, ndef, cnt, old_slot, new_ids, cnt_new, shift_x,
+                     shift_y, shift_z, n, ids, lnk, own, tab, rec);
   return hipGetLastError();
 }
 
