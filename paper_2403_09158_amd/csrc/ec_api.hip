@@ -1131,6 +1131,18 @@ int window_need(const ec_state* st) {
   return std::min(D, st->n / 2);
 }
 
+// The classes and run classes of a new list, in order of first appearance; the
+// class windows and run tables are renewed where the classes changed.
+void renew_classes(ec_state* st, std::vector<DevDefect>& defs) {
+  const std::vector<std::array<double, 6>> old = st->classes;
+  const std::vector<std::array<int, 4>> oldrun = st->runcls;
+  st->classes.clear();
+  st->runcls.clear();
+  assign_classes(st, defs);
+  if (old != st->classes) st->gcls_ncls = -1;
+  if (oldrun != st->runcls) st->gff_nrun = -1;
+}
+
 // Direction classes of the current defect list, assigned on the host (ids in
 // order of first appearance) and written into the device table.
 ec_status ensure_classes(ec_state* st, hipStream_t s) {
@@ -1138,13 +1150,7 @@ ec_status ensure_classes(ec_state* st, hipStream_t s) {
   const size_t nd = st->hdefs.size();
   ec_status r;
   if (nd > 0 && (r = st_grow(st, &st->tags, &st->tags_cap, nd)) != EC_OK) return r;
-  const std::vector<std::array<double, 6>> old = st->classes;
-  const std::vector<std::array<int, 4>> oldrun = st->runcls;
-  st->classes.clear();
-  st->runcls.clear();
-  assign_classes(st, st->hdefs);
-  if (old != st->classes) st->gcls_ncls = -1;
-  if (oldrun != st->runcls) st->gff_nrun = -1;
+  renew_classes(st, st->hdefs);
   if (nd > 0) {
     char* hp = nullptr;
     if ((r = pin_begin(st->pin_tags, nd * sizeof(ClassTag), &hp)) != EC_OK) return r;
@@ -1231,19 +1237,25 @@ RunTables run_tables(const ec_state* st) {
   return t;
 }
 
-// Self-term work-list capacity of the pair path: at most 64 items per defect
-// off the run path, fewer for small boxes (the device plan, from the footprint
-// counts, never needs more); 0 when every defect takes the run path.  The run
-// tables must be current (after ensure_windows).
-int64_t self_work_cap(const ec_state* st) {
+// Self-term work-list capacity of the pair path, and its pairs per item: at
+// most 64 items per defect off the run path, fewer for small boxes (the device
+// plan, from the footprint counts, never needs more); 0 when every defect takes
+// the run path.  The run tables must be current (after ensure_windows).
+int64_t self_work_cap(const ec_state* st, double& target) {
   const int nrun = st->gff_D > 0 ? st->gff_nrun : 0, Dr = st->gff_D;
-  int64_t cap = 0;
-  for (const auto& d : st->hdefs) {
-    if (d.rcls >= 0 && d.rcls < nrun && d.w[0] <= Dr + 1 && d.w[1] <= Dr + 1 && d.w[2] <= Dr + 1) continue;
-    const double m = (double)box_volume(d);
-    const double k = std::ceil(m * (m + 1) / 2 / 32768.0);
-    cap += (int64_t)std::min(64.0, std::max(1.0, k));
-  }
+  auto cap_of = [&](double pairs) {
+    int64_t cap = 0;
+    for (const auto& d : st->hdefs) {
+      if (d.rcls >= 0 && d.rcls < nrun && d.w[0] <= Dr + 1 && d.w[1] <= Dr + 1 && d.w[2] <= Dr + 1) continue;
+      const double m = (double)box_volume(d);
+      const double k = std::ceil(m * (m + 1) / 2 / pairs);
+      cap += (int64_t)std::min(64.0, std::max(1.0, k));
+    }
+    return cap;
+  };
+  target = SELF_PAIRS_FEW;
+  int64_t cap = cap_of(target);
+  if (cap > SELF_FEW_ITEMS) cap = cap_of(target = SELF_PAIRS);
   return cap;
 }
 
@@ -1253,22 +1265,50 @@ ec_status compute_self_terms(ec_state* st, hipStream_t s) {
   if ((r = ensure_windows(st, 0, s)) != EC_OK) return r;
   const WinCache* w = st->win.get();
   const int D = w->D;
-  const int64_t cap = self_work_cap(st);
+  double target = 0.0;
+  const int64_t cap = self_work_cap(st, target);
   if ((r = st_grow(st, &st->work, &st->work_cap, (size_t)std::max<int64_t>(cap, 1))) != EC_OK) return r;
   if ((r = st_grow(st, &st->partial, &st->partial_cap, (size_t)std::max<int64_t>(cap, 1))) != EC_OK) return r;
   if ((r = st_grow(st, &st->wbeg, &st->wbeg_cap, (size_t)st->ndef + 1)) != EC_OK) return r;
   const DefBuf& b = st->db[st->cur];
   LAUNCH(st, s, PF_SELF, 0,
          launch_self_terms(b.tab, st->ndef, b.cnt, b.ids, st->n, w->K, st->gcls, D, run_tables(st), st->work, cap,
-                           st->wbeg, st->partial, st->runsum, st->h3c, st->B, s));
+                           target, st->wbeg, st->partial, st->runsum, st->h3c, st->B, s));
   st->B_valid = true;
   return EC_OK;
 }
 
-// Make stream s wait for self terms still running on the side stream.
+// Polls an event.
+ec_status wait_event(hipEvent_t ev) {
+  hipError_t q;
+  while ((q = hipEventQuery(ev)) == hipErrorNotReady) {
+  }
+  HIPCHK(q);
+  return EC_OK;
+}
+
+// Make stream s wait for self terms still running on the side stream.  Terms
+// that have ended need no wait in the stream (which costs it some ten
+// microseconds).  A stream under capture cannot wait for work outside the
+// capture, so there the host waits for them, in the capture mode that allows it
+// to ask.
 ec_status join_self(ec_state* st, hipStream_t s) {
   if (!st->self_pending) return EC_OK;
-  HIPCHK(hipStreamWaitEvent(s, st->ev_self, 0));
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (s) HIPCHK(hipStreamIsCapturing(s, &cs));
+  if (cs != hipStreamCaptureStatusNone) {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    HIPCHK(hipThreadExchangeStreamCaptureMode(&mode));
+    const ec_status r = wait_event(st->ev_self);
+    HIPCHK(hipThreadExchangeStreamCaptureMode(&mode));
+    if (r != EC_OK) return r;
+  } else {
+    const hipError_t q = hipEventQuery(st->ev_self);
+    if (q == hipErrorNotReady)
+      HIPCHK(hipStreamWaitEvent(s, st->ev_self, 0));
+    else
+      HIPCHK(q);
+  }
   st->self_pending = false;
   return EC_OK;
 }
@@ -1291,15 +1331,6 @@ ec_status self_terms_beside(ec_state* st) {
 ec_status copy_out(void* dst, const void* src, size_t bytes, bool on_device, hipStream_t s) {
   HIPCHK(hipMemcpyAsync(dst, src, bytes, on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, s));
   if (!on_device) HIPCHK(hipStreamSynchronize(s));
-  return EC_OK;
-}
-
-// Polls an event.
-ec_status wait_event(hipEvent_t ev) {
-  hipError_t q;
-  while ((q = hipEventQuery(ev)) == hipErrorNotReady) {
-  }
-  HIPCHK(q);
   return EC_OK;
 }
 
@@ -1486,6 +1517,9 @@ double list_volume(const DevDefect* h, int ndef) {
 // part of the cell.
 bool sparse_rows(const ec_state* st) { return st->fp64 && st->volume < rows_limit(st->n) * (double)st->n3; }
 
+// Cells up to which the self terms go before the passes (solve_table).
+constexpr int64_t EARLY_SELF_VOXELS = 128 * 128 * 128;
+
 // Commits the quantised list h (ndef entries in the pinned staging buffer of
 // the device table, pin_begin already called on it) and solves: footprint
 // slots from the box volumes, the old eigenstrain out and the new one in, the
@@ -1516,6 +1550,21 @@ ec_status solve_table(ec_state* st, DevDefect* h, int32_t ndef, hipStream_t s, b
       (r = st_grow(st, &nb.ids, &idcap, need)) != EC_OK || (r = st_grow(st, &nb.lnk, &lkcap, need)) != EC_OK)
     return r;
   nb.ids_cap = (int64_t)std::min(idcap, lkcap);
+  // small cells: the passes take less than their launches, so the self terms
+  // are queued before them, with the classes already in the uploaded table, and
+  // only what follows the solve waits for them (on larger cells the classes are
+  // assigned while the passes run, and the z pass waits, see below)
+  const bool early = h && ndef > 0 && !keep_self && st->n3 <= EARLY_SELF_VOXELS;
+  std::vector<DevDefect> list;
+  if (early) {
+    list.assign(h, h + ndef);
+    renew_classes(st, list);
+    for (int i = 0; i < ndef; ++i) {
+      h[i].cls = list[i].cls;
+      h[i].rcls = list[i].rcls;
+      h[i].s = list[i].s;
+    }
+  }
   if (ndef > 0 && h) {
     HIPCHK(hipMemcpyAsync(nb.tab, hp, ndef * sizeof(DevDefect), hipMemcpyHostToDevice, s));
     if ((r = pin_end(st->pin_tab, s)) != EC_OK) return r;
@@ -1542,6 +1591,13 @@ ec_status solve_table(ec_state* st, DevDefect* h, int32_t ndef, hipStream_t s, b
     st->jx_ok = false;
   }
   st->jdE_ok = false;
+  if (early) {
+    st->hdefs = std::move(list);
+    st->hcap.resize(ndef);
+    for (int i = 0; i < ndef; ++i) st->hcap[i] = box_volume(h[i]);
+    st->classes_ok = true;
+    if (self_terms_beside(st) != EC_OK) st->B_valid = false;  // left to the next energies call
+  }
   LAUNCH(st, s, PF_OTHER, 0,
          launch_mean_stress(nb.tab, nb.cnt, ndef, st->n3, st->C, st->prob.bc, st->add6, s));
   // Fourier solve.  The self terms run on the side stream beside the forward x and y passes
@@ -1549,6 +1605,7 @@ ec_status solve_table(ec_state* st, DevDefect* h, int32_t ndef, hipStream_t s, b
   // each take most of a CU's LDS, so self-term blocks still resident would
   // hold some of them back and stretch the pass.
   auto beside = [&]() -> ec_status {
+    if (early) return EC_OK;
     // host copies of the list while the device works (the staging buffer is
     // only read by the pending upload); the self-term set-up reads them
     if (h) {
@@ -2144,6 +2201,14 @@ ec_status ec_solve_fields(ec_state* st, const ec_defect* defs, int32_t ndef, voi
       if (bad[c] != INT_MAX) return fail(EC_ERR_ARG, "defect %d: %s", bad[c], why[c].c_str());
   }
   if ((r = solve_table(st, h, ndef, s)) != EC_OK) return r;
+  if (eps_out && sig_out && on_device) {  // both from one pass over the stress
+    if ((r = ensure_sigma(st, s)) != EC_OK) return r;
+    const DefBuf& b = st->db[st->cur];
+    LAUNCH(st, s, PF_OTHER, (st->fp64 ? 144.0 : 96.0) * st->n3,
+           launch_sig_to_out(st->sig, st->own, b.lnk, b.tab, st->ndef, st->n3, st->C, 3, !st->fp64, eps_out, s,
+                             sig_out));
+    return EC_OK;
+  }
   if (eps_out && (r = write_field(st, 1, eps_out, on_device != 0, s)) != EC_OK) return r;
   if (sig_out && (r = write_field(st, 0, sig_out, on_device != 0, s)) != EC_OK) return r;
   return EC_OK;
@@ -2204,14 +2269,15 @@ ec_status ec_interaction_energies_noalloc(ec_state* st, void* stream, double* E_
              launch_run_tables(st->gcls, w->D, Drun, st->runinfo, (int)st->runcls.size(), st->gff, s));
       st->gff_D = Drun;
     }
-    const int64_t cap = self_work_cap(st);
+    double target = 0.0;
+    const int64_t cap = self_work_cap(st, target);
     if (cap > NA_MAX_ITEMS)
       return fail(EC_ERR_SIZE, "the self terms need %lld work items: the no-allocation energies take at most %lld",
                   (long long)cap, (long long)NA_MAX_ITEMS);
     char* base = (char*)st->ctx->scratch;
     LAUNCH(st, s, PF_SELF, 0,
            launch_self_terms(b.tab, st->ndef, b.cnt, b.ids, st->n, w->K, st->gcls, w->D, run_tables(st),
-                             (SelfWork*)(base + NA_WORK_OFF), cap, (int64_t*)(base + NA_WBEG_OFF),
+                             (SelfWork*)(base + NA_WORK_OFF), cap, target, (int64_t*)(base + NA_WBEG_OFF),
                              (double*)(base + NA_PART_OFF), (double*)(base + NA_RUN_OFF), st->h3c, st->B, s));
     st->B_valid = true;
   }

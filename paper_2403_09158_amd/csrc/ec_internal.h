@@ -466,6 +466,13 @@ hipError_t launch_reduce(const DevDefect* d, int ndef, const int32_t* counts, co
                          const double* B, double h3c, double* S6, double* E, double* E2, hipStream_t s);
 hipError_t launch_window_crop(const double* sig, int n, int D, int b, double* K, hipStream_t s);
 hipError_t launch_class_windows(const double* K, int D, const double* dirs, int ncls, double* g, hipStream_t s);
+// Pairs per work item of the pair sums.  Short lists take a quarter of them
+// (SELF_PAIRS_FEW) while their items stay below SELF_FEW_ITEMS, a few per
+// resident workgroup: an item's pairs are one serial chain of gathers per lane,
+// and with few items that chain is the kernel's time (200 defects on 64^3, 40 of
+// them on the pair path: 53 -> 19 us).
+constexpr double SELF_PAIRS = 32768.0, SELF_PAIRS_FEW = 8192.0;
+constexpr int64_t SELF_FEW_ITEMS = 8192;
 // Self-term work item: rows [p0, p1) of defect `def`'s pair triangle.
 struct SelfWork {
   int32_t def, p0, p1, pad;
@@ -493,8 +500,8 @@ struct RunTables {
 // runsum[ndef]).
 hipError_t launch_self_terms(const DevDefect* d, int ndef, const int32_t* counts, const int32_t* ids, int n,
                              const double* K, const double* gcls, int D, RunTables rt, SelfWork* work,
-                             int64_t work_cap, int64_t* wbeg, double* partial, double* runsum, double h3c, double* B,
-                             hipStream_t s);
+                             int64_t work_cap, double target, int64_t* wbeg, double* partial, double* runsum,
+                             double h3c, double* B, hipStream_t s);
 // The run tables of nrun run classes on the half-width Drun <= Dg from the
 // class windows g ((2 Dg + 1)^3 per class).
 hipError_t launch_run_tables(const double* g, int Dg, int Drun, const int4* info, int nrun, double* ff,
@@ -527,9 +534,11 @@ struct ClassTag {
 };
 // Writes tags[i] into defs[i].cls / defs[i].s / defs[i].rcls.
 hipError_t launch_set_class(DevDefect* d, int ndef, const ClassTag* tags, hipStream_t s);
-// which 0: sigma, 1: eps = C^-1:sigma + eps*, 2: eps* alone; out is float or double.
+// which 0: sigma, 1: eps = C^-1:sigma + eps*, 2: eps* alone, 3: eps to out and
+// sigma to out2; out is float or double.
 hipError_t launch_sig_to_out(const double* sig, const int32_t* own, const int2* lnk, const DevDefect* defs, int ndef,
-                             int64_t n3, Cubic C, int which, bool fp32, void* out, hipStream_t s);
+                             int64_t n3, Cubic C, int which, bool fp32, void* out, hipStream_t s,
+                             void* out2 = nullptr);
 
 constexpr int KWIN = 24;  // doubles per window point (21 used: the symmetric 6x6 kernel)
 

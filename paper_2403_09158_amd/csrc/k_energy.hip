@@ -160,13 +160,13 @@ __device__ __forceinline__ int32_t pack_xyz(int id, int n) {
   return (id % n) | (((id / n) % n) << 10) | ((id / (n * n)) << 20);
 }
 
-constexpr double SELF_TARGET = 32768.0;  // pairs per work item
+constexpr double SELF_TARGET = SELF_PAIRS;  // pairs per work item of the cross sums
 constexpr int SELF_KMAX = 64;            // work items per defect at most
 
 // Work items per defect: ceil(m (m + 1) / 2 / target), between 1 and SELF_KMAX.
-__device__ __forceinline__ int self_items_of(int m) {
+__device__ __forceinline__ int self_items_of(int m, double target) {
   const double md = m;
-  const int k = (int)ceil(md * (md + 1.0) * 0.5 / SELF_TARGET);
+  const int k = (int)ceil(md * (md + 1.0) * 0.5 / target);
   return k < 1 ? 1 : (k > SELF_KMAX ? SELF_KMAX : k);
 }
 
@@ -197,8 +197,8 @@ __device__ __forceinline__ bool self_by_runs(const DevDefect& d, int, const RunT
 
 __global__ __launch_bounds__(PT) void k_self_plan(const int32_t* __restrict__ cnt, const DevDefect* __restrict__ defs,
                                                   int ndef, RunTables rt, int64_t* __restrict__ wbeg,
-                                                  SelfWork* __restrict__ work, int64_t cap) {
-  auto items = [&](int i) { return self_by_runs(defs[i], cnt[i], rt) ? 0 : self_items_of(cnt[i]); };
+                                                  SelfWork* __restrict__ work, int64_t cap, double target) {
+  auto items = [&](int i) { return self_by_runs(defs[i], cnt[i], rt) ? 0 : self_items_of(cnt[i], target); };
   __shared__ int64_t part[2 * (PT / 64)];
   const int per = (ndef + PT - 1) / PT;
   const int b = threadIdx.x * per, e = min(ndef, b + per);
@@ -917,12 +917,13 @@ __global__ __launch_bounds__(RDT) void k_dipole(const DevDefect* __restrict__ de
 
 // Dense component-major outputs [6][n^3] from the voxel-major sigma: which
 // 0 -> sigma, 1 -> eps = C^-1:sigma + eps* (cubic compliance, in the cube
-// frame for a rotated crystal), 2 -> eps*
-// (owner-list gather).
+// frame for a rotated crystal), 2 -> eps* (owner-list gather), 3 -> eps to out
+// and sigma to out2 from one reading of sigma (bound by HBM: 160^3 FP32, 393 MB,
+// 75 us; 115 for the two by themselves).
 template <typename OT>
 __global__ void k_sig_to_out(const double* __restrict__ sig, const int32_t* __restrict__ own,
                              const int2* __restrict__ lnk, const DevDefect* __restrict__ defs, int max_links,
-                             int64_t n3, Cubic C, int which, OT* __restrict__ out) {
+                             int64_t n3, Cubic C, int which, OT* __restrict__ out, OT* __restrict__ out2) {
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= n3) return;
   double es[6] = {0, 0, 0, 0, 0, 0};
@@ -940,10 +941,11 @@ __global__ void k_sig_to_out(const double* __restrict__ sig, const int32_t* __re
   }
   double s[6];
   ld_voxel(sig, t, s);
-  if (which == 0) {
+  if (which == 0 || which == 3) {
+    OT* const o = which == 0 ? out : out2;
 #pragma unroll
-    for (int a = 0; a < 6; ++a) out[a * n3 + t] = (OT)s[a];
-    return;
+    for (int a = 0; a < 6; ++a) o[a * n3 + t] = (OT)s[a];
+    if (which == 0) return;
   }
   const double den = (C.C11 - C.C12) * (C.C11 + 2.0 * C.C12);
   const double S11 = (C.C11 + C.C12) / den, S12 = -C.C12 / den, S44h = 0.5 / C.C44;
@@ -1016,8 +1018,8 @@ hipError_t launch_class_windows(const double* K, int D, const double* dirs, int 
 
 hipError_t launch_self_terms(const DevDefect* d, int ndef, const int32_t* counts, const int32_t* ids, int n,
                              const double* K, const double* gcls, int D, RunTables rt, SelfWork* work,
-                             int64_t work_cap, int64_t* wbeg, double* partial, double* runsum, double h3c, double* B,
-                             hipStream_t s) {
+                             int64_t work_cap, double target, int64_t* wbeg, double* partial, double* runsum,
+                             double h3c, double* B, hipStream_t s) {
   if (ndef == 0) return hipSuccess;
   const int g1 = (ndef + 255) / 256;
   if (rt.nrun > 0) {
@@ -1028,7 +1030,8 @@ hipError_t launch_self_terms(const DevDefect* d, int ndef, const int32_t* counts
   // the pair path only for the defects off the run path (work_cap bounds their
   // items; none: neither the plan nor the pair kernel runs)
   if (work_cap > 0) {
-    hipLaunchKernelGGL(k_self_plan, dim3(1), dim3(PT), 0, s, counts, d, ndef, rt, wbeg, work, work_cap);
+    hipLaunchKernelGGL(k_self_plan, dim3(1), dim3(PT), 0, s, counts, d, ndef, rt, wbeg, work, work_cap,
+                       target);
     const int grid = (int)std::min<int64_t>(work_cap, 4096);
     hipLaunchKernelGGL(k_self, dim3(grid), dim3(ST), 0, s, d, counts, ids, n, K, gcls, D, work, wbeg + ndef,
                        work_cap, partial);
@@ -1114,14 +1117,14 @@ hipError_t launch_dipole(const DevDefect* d, int ndef, const int32_t* counts, co
 }
 
 hipError_t launch_sig_to_out(const double* sig, const int32_t* own, const int2* lnk, const DevDefect* defs, int ndef,
-                             int64_t n3, Cubic C, int which, bool fp32, void* out, hipStream_t s) {
+                             int64_t n3, Cubic C, int which, bool fp32, void* out, hipStream_t s, void* out2) {
   const unsigned grid = (unsigned)((n3 + 255) / 256);
   if (fp32)
     hipLaunchKernelGGL(k_sig_to_out<float>, dim3(grid), dim3(256), 0, s, sig, own, lnk, defs, ndef, n3, C, which,
-                       (float*)out);
+                       (float*)out, (float*)out2);
   else
     hipLaunchKernelGGL(k_sig_to_out<double>, dim3(grid), dim3(256), 0, s, sig, own, lnk, defs, ndef, n3, C, which,
-                       (double*)out);
+                       (double*)out, (double*)out2);
   return hipGetLastError();
 }
 

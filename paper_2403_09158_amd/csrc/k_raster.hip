@@ -13,7 +13,7 @@ namespace ec {
 
 namespace {
 
-constexpr int RT = 256;  // threads per rasteriser workgroup
+constexpr int RT = 256;  // threads per workgroup of the list kernels
 
 // Exclusive scan of counts into offsets[0..ndef] (offsets[ndef] = total); one workgroup.
 __global__ __launch_bounds__(1024) void k_scan(const int32_t* __restrict__ counts, int ndef,
@@ -57,6 +57,11 @@ __global__ __launch_bounds__(1024) void k_scan(const int32_t* __restrict__ count
 // each thread tests one candidate at a time.  A ballot scan gives every member
 // its place, so the footprint list comes out sorted with no per-row serial
 // work, and the atomics of a pass are independent of each other.
+//
+// T threads: a defect's candidates are a chain of passes of the workgroup, so
+// few defects take wider ones (488 on 160^3: 19 -> 15 us with 512 threads), while
+// many fill the chip with narrow ones (20000 on 512^3: 279 us with 256, 336 with
+// 512).
 constexpr int RCH = 1024;
 
 __device__ __forceinline__ void row_yz(const DevDefect& d, int n, int r, int& y, int& z) {
@@ -65,16 +70,17 @@ __device__ __forceinline__ void row_yz(const DevDefect& d, int n, int r, int& y,
   z = box_axis(d.lo[2], d.w[2], n, iz);
 }
 
-__global__ __launch_bounds__(RT) void k_raster_fill(const DevDefect* __restrict__ defs, int n,
+template <int T>
+__global__ __launch_bounds__(T) void k_raster_fill(const DevDefect* __restrict__ defs, int n,
                                                     int32_t* __restrict__ ids, int2* __restrict__ lnk,
                                                     int32_t* __restrict__ counts, int32_t* __restrict__ own) {
   const DevDefect d = defs[blockIdx.x];
   const int nrows = d.w[1] * d.w[2];
   __shared__ int roff[RCH + 1];  // candidates before each row of the chunk
   __shared__ int rxa[RCH];       // first candidate x of each row, unwrapped (may be >= n)
-  __shared__ int wsum[RT / 64];
+  __shared__ int wsum[T / 64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  constexpr int PER = RCH / RT;
+  constexpr int PER = RCH / T;
   int run = 0;  // members placed so far (same value in every thread)
   for (int r0 = 0; r0 < nrows; r0 += RCH) {
     const int nr = min(RCH, nrows - r0);
@@ -96,13 +102,13 @@ __global__ __launch_bounds__(RT) void k_raster_fill(const DevDefect* __restrict_
     }
     int incl = s;
     for (int o = 1; o < 64; o <<= 1) {
-      const int t = __shfl_up(incl, o);
-      if (lane >= o) incl += t;
+      const int up = __shfl_up(incl, o);
+      if (lane >= o) incl += up;
     }
     if (lane == 63) wsum[wave] = incl;
     __syncthreads();
     int acc = incl - s, ctot = 0;
-    for (int w = 0; w < RT / 64; ++w) {
+    for (int w = 0; w < T / 64; ++w) {
       if (w < wave) acc += wsum[w];
       ctot += wsum[w];
     }
@@ -114,7 +120,7 @@ __global__ __launch_bounds__(RT) void k_raster_fill(const DevDefect* __restrict_
     }
     if (threadIdx.x == 0) roff[nr] = ctot;
     __syncthreads();
-    for (int k0 = 0; k0 < ctot; k0 += RT) {
+    for (int k0 = 0; k0 < ctot; k0 += T) {
       const int k = k0 + threadIdx.x;
       bool is = false;
       int id = 0;
@@ -143,7 +149,7 @@ __global__ __launch_bounds__(RT) void k_raster_fill(const DevDefect* __restrict_
       if (lane == 0) wsum[wave] = __popcll(m);
       __syncthreads();
       int before = __popcll(m & ((1ull << lane) - 1)), tot = 0;
-      for (int w = 0; w < RT / 64; ++w) {
+      for (int w = 0; w < T / 64; ++w) {
         if (w < wave) before += wsum[w];
         tot += wsum[w];
       }
@@ -278,40 +284,54 @@ __global__ __launch_bounds__(64) void k_set_records(const HopJob* __restrict__ j
 // sigma gets -C:<eps*>, <eps*> = (1/n^3) sum_i |Omega_i| E_i, compensated FP64
 // sums over a fixed partition of the defects (deterministic).  Mean stress
 // zero: nothing to add (the host does not launch this kernel).
-constexpr int MT = 256;
+// One workgroup: each thread sums its defects, each wavefront its lanes by
+// shuffles, and six threads one component each over the wavefronts (200 to 20000
+// defects take a few microseconds; a combine by one thread over all threads'
+// sums took 48).
+constexpr int MT = 1024;
+
+__device__ __forceinline__ void add_comp(double& s, double& c, double v) {  // Neumaier
+  const double t = s + v;
+  c += (fabs(s) >= fabs(v)) ? ((s - t) + v) : ((v - t) + s);
+  s = t;
+}
+
 __global__ __launch_bounds__(MT) void k_mean_stress(const DevDefect* __restrict__ defs,
                                                     const int32_t* __restrict__ counts, int ndef, double inv_n3,
                                                     Cubic C, double* __restrict__ add6) {
-  __shared__ double ps[6][MT], pc[6][MT];
+  __shared__ double ps[6][MT / 64], pc[6][MT / 64], m[6];
   double s[6], c[6];
+#pragma unroll
   for (int a = 0; a < 6; ++a) s[a] = c[a] = 0.0;
   for (int i = threadIdx.x; i < ndef; i += MT) {
     const double k = (double)counts[i];
-    for (int a = 0; a < 6; ++a) {
-      const double v = k * defs[i].E[a];
-      const double t = s[a] + v;
-      c[a] += (fabs(s[a]) >= fabs(v)) ? ((s[a] - t) + v) : ((v - t) + s[a]);
-      s[a] = t;
-    }
+#pragma unroll
+    for (int a = 0; a < 6; ++a) add_comp(s[a], c[a], k * defs[i].E[a]);
   }
-  for (int a = 0; a < 6; ++a) {
-    ps[a][threadIdx.x] = s[a];
-    pc[a][threadIdx.x] = c[a];
+  for (int off = 32; off > 0; off >>= 1)
+#pragma unroll
+    for (int a = 0; a < 6; ++a) {
+      const double s2 = __shfl_down(s[a], off), c2 = __shfl_down(c[a], off);
+      add_comp(s[a], c[a], s2);
+      c[a] += c2;
+    }
+  if ((threadIdx.x & 63) == 0)
+#pragma unroll
+    for (int a = 0; a < 6; ++a) {
+      ps[a][threadIdx.x >> 6] = s[a];
+      pc[a][threadIdx.x >> 6] = c[a];
+    }
+  __syncthreads();
+  if (threadIdx.x < 6) {
+    double ss = 0.0, cc = 0.0;
+    for (int w = 0; w < MT / 64; ++w) {
+      add_comp(ss, cc, ps[threadIdx.x][w]);
+      cc += pc[threadIdx.x][w];
+    }
+    m[threadIdx.x] = (ss + cc) * inv_n3;
   }
   __syncthreads();
   if (threadIdx.x != 0) return;
-  double m[6];
-  for (int a = 0; a < 6; ++a) {
-    double ss = 0.0, cc = 0.0;
-    for (int t = 0; t < MT; ++t) {
-      const double v = ps[a][t];
-      const double u = ss + v;
-      cc += (fabs(ss) >= fabs(v)) ? ((ss - u) + v) : ((v - u) + ss);
-      ss = u;
-      cc += pc[a][t];
-    }
-    m[a] = (ss + cc) * inv_n3;
-  }
   double mc[6], t[6];
   if (C.frm)
     rot6(C.frm, m, mc);  // the mean eigenstrain in the cube frame
@@ -347,7 +367,10 @@ hipError_t launch_scan(const int32_t* counts, int ndef, int64_t* offsets, hipStr
 hipError_t launch_raster_fill(const DevDefect* d, int ndef, int n, int32_t* ids, int2* lnk, int32_t* counts,
                               int32_t* own, hipStream_t s) {
   if (ndef == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_raster_fill, dim3(ndef), dim3(RT), 0, s, d, n, ids, lnk, counts, own);
+  if (ndef < 1024)
+    hipLaunchKernelGGL(k_raster_fill<512>, dim3(ndef), dim3(512), 0, s, d, n, ids, lnk, counts, own);
+  else
+    hipLaunchKernelGGL(k_raster_fill<256>, dim3(ndef), dim3(256), 0, s, d, n, ids, lnk, counts, own);
   return hipGetLastError();
 }
 
