@@ -3047,43 +3047,19 @@ ec_status ec_type_energies(ec_state* st, int32_t type, const double* X, int32_t 
   if (e == hipSuccess) e = launch_pencil(fp64, false, 1, st->spec, st->g, full, st->tw, nullptr, s);
   if (e == hipSuccess) e = launch_pencil(fp64, false, 2, st->spec, st->g, full, st->tw, nullptr, s);
   if (e != hipSuccess) return fail(EC_ERR_DEVICE, "HIP error %s", hipGetErrorString(e));
-  // phase factors exp(-2 pi i l d / L) per axis and label l (the centred label
-  // of each bin, -n/2 at an even n's Nyquist bin; +n/2 in the second table)
-  std::vector<double2> htab(ntab), hnyq(nnyq);
-  auto factor = [&](int l, double u) {
-    double t = (double)l * u;
-    t -= std::floor(t);
-    return make_double2(std::cos(2.0 * M_PI * t), -std::sin(2.0 * M_PI * t));
-  };
-  auto fill = [&](int p, const double* Xp) {
-    for (int a = 0; a < 3; ++a) {
-      const double u = (Xp[a] - T.X0[a]) / L;
-      double2* row = htab.data() + ((size_t)p * 3 + a) * n;
-      for (int q = 0; q < n; ++q) row[q] = factor(q <= (n - 1) / 2 ? q : q - n, u);
-      hnyq[(size_t)p * 3 + a] = factor(n / 2, u);
-    }
-  };
   const double scale = -st->h3c / (double)st->n3;
-  for (int p0 = 0; p0 < k; p0 += TYPE_NP) {
+  for (int p0 = 0; p0 < k && e == hipSuccess; p0 += TYPE_NP) {
     const int np = std::min(TYPE_NP, k - p0);
-    if (p0 > 0 && (e = hipStreamSynchronize(s)) != hipSuccess) break;  // the host tables are refilled
-    for (int p = 0; p < np; ++p) fill(p, X + 3 * (size_t)(p0 + p));
-    if (X_excl) fill(np, X_excl);
-    const size_t rows = (size_t)(np + (X_excl ? 1 : 0));
-    if ((e = hipMemcpyAsync(dtab, htab.data(), rows * 3 * n * sizeof(double2), hipMemcpyHostToDevice, s)) !=
-            hipSuccess ||
-        (e = hipMemcpyAsync(dnyq, hnyq.data(), rows * 3 * sizeof(double2), hipMemcpyHostToDevice, s)) !=
-            hipSuccess)
-      break;
-    // the excluded mover's factors sit in entry np of the tables
-    if ((e = launch_type_energies(fp64, st->spec, T.eps, T.sig, st->g, dtab, dnyq, np, X_excl != nullptr, partial,
-                                  scale, dE + p0, s)) != hipSuccess)
-      break;
+    TypeOffsets off{};
+    for (int a = 0; a < 3; ++a) {
+      for (int p = 0; p < np; ++p) off.u[3 * p + a] = (X[3 * (size_t)(p0 + p) + a] - T.X0[a]) / L;
+      if (X_excl) off.u[3 * np + a] = (X_excl[a] - T.X0[a]) / L;
+    }
+    e = launch_type_energies(fp64, st->spec, T.eps, T.sig, st->g, off, dtab, dnyq, np, X_excl != nullptr, partial,
+                             scale, dE + p0, s);
   }
-  if (e == hipSuccess) e = hipMemcpyAsync(E_out, dE, (size_t)k * 8, hipMemcpyDeviceToHost, s);
-  if (e == hipSuccess) e = hipStreamSynchronize(s);
-  if (e != hipSuccess) return fail(EC_ERR_DEVICE, "HIP error %s", hipGetErrorString(e));
-  return EC_OK;
+  if (e == hipSuccess) return copy_small(st, E_out, dE, (size_t)k * 8, false, s);
+  return fail(EC_ERR_DEVICE, "HIP error %s", hipGetErrorString(e));
 }
 
 ec_status ec_debug_forward(ec_state* st, const double* field, double* out) {
