@@ -30,24 +30,31 @@ __device__ __forceinline__ double2 cmul2(double2 a, double2 b) {
   return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
 }
 
-// Phase tables: tab[(p * 3 + a) * n + k] is the factor exp(-2 pi i l u) of axis
-// a at bin k for entry p (u the offset along the axis over the cell side, l the
-// centred label, -n/2 at an even n's Nyquist bin), nyq[p * 3 + a] the factor of
-// the +n/2 representative.
-__global__ __launch_bounds__(TT) void k_type_tables(TypeOffsets off, int rows, int n, double2* __restrict__ tab,
-                                                    double2* __restrict__ nyq) {
+// Phase tables: the factor exp(-2 pi i l u) of axis a at bin k for entry p (u the
+// offset along the axis over the cell side, l the centred label, -n/2 at an even
+// n's Nyquist bin) stands at tab[phase_at(p, a, k, n)]: rows of k for x and y,
+// the entries of a kz side by side for z (read together by scalar loads);
+// nyq[p * 3 + a] is the factor of the +n/2 representative.  Entries are the np
+// positions and, at TYPE_NP, the excluded mover (offset np).
+__host__ __device__ inline size_t phase_at(int p, int a, int k, int n) {
+  return a < 2 ? ((size_t)p * 2 + a) * n + k : (size_t)(TYPE_NP + 1) * (2 * n + k) + p;
+}
+
+__global__ __launch_bounds__(TT) void k_type_tables(TypeOffsets off, int rows, int np, int n,
+                                                    double2* __restrict__ tab, double2* __restrict__ nyq) {
   const int t = blockIdx.x * TT + threadIdx.x;
-  if (t >= 3 * rows * (n + 1)) return;
+  if (t >= rows * (n + 1)) return;
   const int r = t / (n + 1), q = t % (n + 1);
   const int l = q == n ? n / 2 : (q <= (n - 1) / 2 ? q : q - n);
   double v = (double)l * off.u[r];
   v -= floor(v);
   double sn, cs;
   sincospi(2.0 * v, &sn, &cs);
+  const int p = r / 3 == np ? TYPE_NP : r / 3, a = r % 3;
   if (q == n)
-    nyq[r] = make_double2(cs, -sn);
+    nyq[3 * p + a] = make_double2(cs, -sn);
   else
-    tab[(size_t)r * n + q] = make_double2(cs, -sn);
+    tab[phase_at(p, a, q, n)] = make_double2(cs, -sn);
 }
 
 // One thread per column (kx, ky) and chunk of kz.  A column's phase is the
@@ -56,7 +63,7 @@ __global__ __launch_bounds__(TT) void k_type_tables(TypeOffsets off, int rows, i
 // alike), and the z factor, the same for all lanes: a bin costs each position
 // one complex product and two multiply-adds, where three table reads and two
 // products per bin and position had bound the pass (128^3 FP32, 16 positions:
-// 95 us against 26 for the spectra's 152 MB; now 34).  At the Nyquist plane of
+// 95 us against 26 for the spectra's 152 MB; now 57).  At the Nyquist plane of
 // an even n the two representatives have z factors of their own.
 template <typename S, bool EXCL>
 __global__ __launch_bounds__(TT) void k_type_energy(const typename Cplx<S>::T* __restrict__ sig,
@@ -75,10 +82,9 @@ __global__ __launch_bounds__(TT) void k_type_energy(const typename Cplx<S>::T* _
   const bool live = col < n * NH;
   const int kx = live ? col % NH : 0, ky = live ? col / NH : 0;
   const bool nx = even && kx == n / 2, ny = even && ky == n / 2;
-  auto entry = [&](int j) { return j < TYPE_NP ? j : np; };  // row of phase j in the tables
   auto xy = [&](int e, bool second) {
-    const double2* t = tab + (size_t)e * 3 * n;
-    const double2 a = second && nx ? nyq[3 * e] : t[kx], b = second && ny ? nyq[3 * e + 1] : t[n + ky];
+    const double2 a = second && nx ? nyq[3 * e] : tab[phase_at(e, 0, kx, n)];
+    const double2 b = second && ny ? nyq[3 * e + 1] : tab[phase_at(e, 1, ky, n)];
     return cmul2(a, b);
   };
   double2 f[NX];
@@ -86,9 +92,9 @@ __global__ __launch_bounds__(TT) void k_type_energy(const typename Cplx<S>::T* _
   for (int j = 0; j < NX; ++j) {
     f[j] = make_double2(0.0, 0.0);
     if (j < np || j == TYPE_NP) {
-      f[j] = xy(entry(j), false);
+      f[j] = xy(j, false);
       if (nx || ny) {
-        const double2 g = xy(entry(j), true);
+        const double2 g = xy(j, true);
         f[j] = make_double2(0.5 * (f[j].x + g.x), 0.5 * (f[j].y + g.y));
       }
     }
@@ -97,26 +103,29 @@ __global__ __launch_bounds__(TT) void k_type_energy(const typename Cplx<S>::T* _
   double acc[TYPE_NP];
 #pragma unroll
   for (int p = 0; p < TYPE_NP; ++p) acc[p] = 0.0;
-  for (int kz = z0; kz < z1; ++kz) {
-    const bool nz = even && kz == n / 2;
-    auto phase = [&](int j) {
-      const int e = entry(j);
-      const double2 c = tab[((size_t)e * 3 + 2) * n + kz];
-      if (!nz) return cmul2(f[j], c);
-      const double2 m0 = cmul2(xy(e, false), c), m1 = cmul2(xy(e, true), nyq[3 * e + 2]);
-      return make_double2(0.5 * (m0.x + m1.x), 0.5 * (m0.y + m1.y));
-    };
+  struct Bin {
+    typename Cplx<S>::T e[6], s[6], q[EXCL ? 6 : 1];
+  };
+  auto load = [&](int kz, Bin& v) {
     const size_t o = spec_at(kz, ky, kx, 0, n, P);
+#pragma unroll
+    for (int c = 0; c < 6; ++c) {
+      v.e[c] = te[o + c];
+      v.s[c] = sig[o + c];
+      if constexpr (EXCL) v.q[c] = ts[o + c];
+    }
+  };
+  auto add = [&](const Bin& v, auto&& phase) {
     // A = eps*_hat_0 : conj(sigma_hat), B = eps*_hat_0 : conj(sigma_hat_0)
     double2 A = make_double2(0.0, 0.0), B = make_double2(0.0, 0.0);
 #pragma unroll
     for (int c = 0; c < 6; ++c) {
       const double w = c < 3 ? 1.0 : 2.0;
-      const double2 e = ld2(te + o + c), s = ld2(sig + o + c);
+      const double2 e = ld2(&v.e[c]), s = ld2(&v.s[c]);
       A.x += w * (e.x * s.x + e.y * s.y);
       A.y += w * (e.y * s.x - e.x * s.y);
       if constexpr (EXCL) {
-        const double2 q = ld2(ts + o + c);
+        const double2 q = ld2(&v.q[c]);
         B.x += w * (e.x * q.x + e.y * q.y);
         B.y += w * (e.y * q.x - e.x * q.y);
       }
@@ -135,6 +144,27 @@ __global__ __launch_bounds__(TT) void k_type_energy(const typename Cplx<S>::T* _
         acc[p] += g.x * A.x - g.y * A.y;
       }
     }
+  };
+  // the next plane's values are loaded while this one's are added; an even n's
+  // Nyquist plane comes last, by itself
+  const int zn = even ? n / 2 : -1;
+  auto after = [&](int kz) { return kz + 1 == zn ? kz + 2 : kz + 1; };
+  Bin v, w;
+  int kz = z0 == zn ? z0 + 1 : z0;
+  if (kz < z1) load(kz, v);
+  while (kz < z1) {
+    const int kn = after(kz);
+    load(kn < z1 ? kn : kz, w);
+    add(v, [&](int j) { return cmul2(f[j], tab[phase_at(j, 2, kz, n)]); });
+    v = w;
+    kz = kn;
+  }
+  if (z0 <= zn && zn < z1) {
+    load(zn, v);
+    add(v, [&](int j) {
+      const double2 m0 = cmul2(xy(j, false), tab[phase_at(j, 2, zn, n)]), m1 = cmul2(xy(j, true), nyq[3 * j + 2]);
+      return make_double2(0.5 * (m0.x + m1.x), 0.5 * (m0.y + m1.y));
+    });
   }
   // block sums by a fixed tree
 #pragma unroll
@@ -196,7 +226,8 @@ hipError_t launch_type_energies(bool fp64, const void* sig, const void* te, cons
                                 double scale, double* E, hipStream_t s) {
   if (np < 1 || np > TYPE_NP) return hipErrorInvalidValue;
   const int n = g.n, rows = 3 * (np + (excl ? 1 : 0));
-  hipLaunchKernelGGL(k_type_tables, dim3((rows * (n + 1) + TT - 1) / TT), dim3(TT), 0, s, off, rows / 3, n, tab, nyq);
+  hipLaunchKernelGGL(k_type_tables, dim3((rows * (n + 1) + TT - 1) / TT), dim3(TT), 0, s, off, rows, np, n, tab,
+                     nyq);
   const int grid = type_energy_grid(n), chunk = type_chunk(n);
   auto go = [&](auto* k, auto* sp) {
     using C2 = std::remove_pointer_t<decltype(sp)>;
