@@ -548,6 +548,59 @@ __device__ __forceinline__ void transform_plan(const TW& tw, Load0&& load0, LdsL
   }
 }
 
+// Whether a length takes transform_half: a two-stage plan without a direct
+// radix whose stages give a thread at most one butterfly each.
+template <int N, int NFFT, int T>
+constexpr bool half_plan() {
+  constexpr Plan2 P = plan_of(N);
+  return P.nstage == 2 && !has_direct(P) && NFFT * (N / P.r[0]) <= T && NFFT * (N / P.r[1]) <= T;
+}
+
+// Two-stage transform whose exchange goes through LDS in two halves, the real
+// parts and then the imaginary parts, so that it takes half the LDS of an
+// exchange of complex values (and more workgroups fit a CU) for two more
+// barriers.  at(f, i): the LDS entry of element i of transform f.  The values
+// are those of transform().
+template <int N, bool INV, Map M, int NFFT, int T, class TW, class Load0, class At, class StoreLast>
+__device__ __forceinline__ void transform_half(const TW& tw, Load0&& load0, At&& at, StoreLast&& store_last) {
+  constexpr Plan2 P = plan_of(N);
+  constexpr int R0 = P.r[0], R1 = P.r[1];
+  static_assert(half_plan<N, NFFT, T>(), "one butterfly per thread and stage");
+  const int tid = threadIdx.x;
+  const bool in0 = NFFT * (N / R0) == T || tid < NFFT * (N / R0), in1 = NFFT * (N / R1) == T || tid < NFFT * (N / R1);
+  int f0, j0, f1, j1;
+  bfly_index<M, N, R0, NFFT, NFFT>(tid, f0, j0);
+  bfly_index<M, N, R1, NFFT, NFFT>(tid, f1, j1);
+  double2 v[R0], u[R1];
+  if (in0) {
+#pragma unroll
+    for (int r = 0; r < R0; ++r) v[r] = load0(f0, j0 + r * (N / R0));
+    Dft<R0, INV>::run(v);
+#pragma unroll
+    for (int r = 0; r < R0; ++r) *at(f0, j0 * R0 + r) = v[r].x;
+  }
+  __syncthreads();
+  if (in1)
+#pragma unroll
+    for (int r = 0; r < R1; ++r) u[r].x = *at(f1, j1 + r * (N / R1));
+  __syncthreads();
+  if (in0)
+#pragma unroll
+    for (int r = 0; r < R0; ++r) *at(f0, j0 * R0 + r) = v[r].y;
+  __syncthreads();
+  if (in1) {
+    const int k = j1 % R0;
+#pragma unroll
+    for (int r = 0; r < R1; ++r) u[r].y = *at(f1, j1 + r * (N / R1));
+#pragma unroll
+    for (int r = 1; r < R1; ++r) u[r] = cmul(u[r], twiddle<INV>(tw, r, k * r * (N / (R0 * R1))));
+    Dft<R1, INV>::run(u);
+    const int base = (j1 / R0) * R0 * R1 + k;
+#pragma unroll
+    for (int r = 0; r < R1; ++r) store_last(f1, base + r * R0, u[r], r);
+  }
+}
+
 // Factorisation for the fused z pass: radices whose butterfly counts divide
 // evenly over the workgroup when six components are transformed together.
 __host__ __device__ constexpr Plan2 plan_fused(int N) {

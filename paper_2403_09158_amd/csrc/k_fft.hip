@@ -1174,11 +1174,26 @@ __global__ __launch_bounds__(256) void k_green(typename Cplx<S>::T* __restrict__
 // held.  keep = 0 stores every voxel: the pass that forms the whole field runs
 // this same code, so a covered voxel gets the same bits either way (separate
 // code for the two could fuse multiplies and adds differently).
+//
+// With FP32 storage the exchange between two stages goes through half the LDS
+// (transform_half): the workgroups of two or three wavefronts were limited to
+// ten wavefronts per CU by their LDS (256^3 covered-voxel pass 172 -> 159 us; with
+// registers for four wavefronts per SIMD, which spills at 256 and with FP64
+// storage, 240^3 146 -> 123; FP64 storage loses, 256^3 244 -> 268).
+template <int N, typename S>
+constexpr bool xi_half() {
+  return sizeof(S) == 4 && half_plan<N, 3 * x_rows(N), pick_T(max_nb(N, 3 * x_rows(N)))>();
+}
+template <int N, typename S, bool ACC>
+constexpr int xi_waves() {
+  return ACC ? 1 : xi_half<N, S>() ? (N < 256 ? 4 : 1) : sizeof(S) == 4 ? min_waves<N>() : 1;
+}
+
 // SWAP (with ACC): the stress replaces the one in sig, and the total it is part
 // of is renewed with it, total = (total - old) + new.
 template <int N, typename S, bool ACC, bool BG, bool BATCH = false, bool MASK = false, bool SWAP = false>
 __global__ __launch_bounds__(pick_T(max_nb(N, 3 * x_rows(N))))
-__attribute__((amdgpu_waves_per_eu(sizeof(S) == 4 && !ACC ? min_waves<N>() : 1))) void k_x_inverse(
+__attribute__((amdgpu_waves_per_eu(xi_waves<N, S, ACC>()))) void k_x_inverse(
     const typename Cplx<S>::T* __restrict__ spec, double* __restrict__ sig, const double* __restrict__ mean6,
     const double2* __restrict__ twg, const double* __restrict__ bg, int bg_mask,
     const HopJob* __restrict__ jobs = nullptr, const double* add3 = nullptr,
@@ -1190,7 +1205,8 @@ __attribute__((amdgpu_waves_per_eu(sizeof(S) == 4 && !ACC ? min_waves<N>() : 1))
   constexpr int P = spec_pitch(N, sizeof(S) == 8);
   constexpr int N3 = N * N * N;
   static_assert(6LL * N * N * P < (1LL << 31) && 6LL * N3 < (1LL << 31), "32-bit element offsets");
-  __shared__ double2 buf[NF * LDN];
+  constexpr bool HALF = xi_half<N, S>();
+  __shared__ std::conditional_t<HALF, double, double2> buf[NF * LDN];
   __shared__ double2 tw[N];
   __shared__ double mean_s[6];
   for (int i = threadIdx.x; i < N; i += T) tw[i] = twg[i];
@@ -1221,8 +1237,6 @@ __attribute__((amdgpu_waves_per_eu(sizeof(S) == 4 && !ACC ? min_waves<N>() : 1))
     }
     return make_double2(A.x - B.y, A.y + B.x);
   };
-  auto from_lds = [&](int f, int i) { return buf[f * LDN + i + (i >> 4)]; };
-  auto to_lds = [&](int f, int i, double2 v) { buf[f * LDN + i + (i >> 4)] = v; };
   // sigma is voxel-major, [n^3][6]: components 2p and 2p+1 of a voxel are one
   // aligned 16-byte pair, and the lanes of a store cover whole voxel records
   auto sig_at = [&](int f, int x) -> double2* {
@@ -1240,21 +1254,23 @@ __attribute__((amdgpu_waves_per_eu(sizeof(S) == 4 && !ACC ? min_waves<N>() : 1))
   constexpr int NSL = PLX.nstage == 1 ? 1 : (PLX.nstage == 2 ? PLX.r[0] : PLX.r[0] * PLX.r[1]);
   constexpr int NOUT = ((NF * (N / RL) + T - 1) / T) * RL;
   double2 old[ACC ? NOUT : 1];
-  int32_t ow[MASK ? NOUT : 1];
+  static_assert(NOUT <= 64, "one bit per output");
+  uint64_t covered = 0;  // bit per output: some defect covers its voxel
   if constexpr (MASK) {
-    bool any = false;
+    int32_t ow[NOUT];
     for_outputs<N, RL, NSL, Map::Row, NF, T>([&](int f, int x, int slot) {
       // keep = 0 (every voxel): the loads all read the map's first entry, one
       // cached line, instead of the whole map
       ow[slot] = own[((z * N + y0 + f / 3) * N + x) & keep] & keep;
-      any |= ow[slot] != -1;
     });
+    for_outputs<N, RL, NSL, Map::Row, NF, T>(
+        [&](int, int, int slot) { covered |= (uint64_t)(ow[slot] != -1) << slot; });
     // rows that no defect covers store nothing: their transform is skipped
-    if (!__syncthreads_or(any)) return;
+    if (!__syncthreads_or(covered != 0)) return;
   }
   if constexpr (ACC)
     for_outputs<N, RL, NSL, Map::Row, NF, T>([&](int f, int x, int slot) {
-      if (!MASK || ow[slot] != -1)
+      if (!MASK || (covered >> slot & 1))
       {
         old[slot] = add_at(f, x);
         if constexpr (SWAP) {  // the total without the old stress
@@ -1267,7 +1283,7 @@ __attribute__((amdgpu_waves_per_eu(sizeof(S) == 4 && !ACC ? min_waves<N>() : 1))
     });
   auto store_last = [&](int f, int x, double2 v, int slot) {
     if constexpr (MASK)
-      if (ow[slot] == -1) return;
+      if (!(covered >> slot & 1)) return;
     const int p = f % 3, y = y0 + f / 3;
     double2* s01 = sig_at(f, x);
     double2 r = make_double2(v.x * scale + mean_s[2 * p], v.y * scale + mean_s[2 * p + 1]);
@@ -1291,7 +1307,14 @@ __attribute__((amdgpu_waves_per_eu(sizeof(S) == 4 && !ACC ? min_waves<N>() : 1))
     }
     *s01 = r;
   };
-  transform<N, true, Map::Row, NF, T>(tw, load0, from_lds, to_lds, store_last);
+  if constexpr (HALF) {
+    transform_half<N, true, Map::Row, NF, T>((const double2*)tw, load0,
+                                             [&](int f, int i) { return &buf[f * LDN + i + (i >> 4)]; }, store_last);
+  } else {
+    auto from_lds = [&](int f, int i) { return buf[f * LDN + i + (i >> 4)]; };
+    auto to_lds = [&](int f, int i, double2 v) { buf[f * LDN + i + (i >> 4)] = v; };
+    transform<N, true, Map::Row, NF, T>(tw, load0, from_lds, to_lds, store_last);
+  }
 }
 
 // ------------------------------------------------------------------ launchers
