@@ -1139,6 +1139,203 @@ void k_zgreen(typename Cplx<S>::T* __restrict__ spec, Cubic C,
   }
 }
 
+// The fused pass with half the LDS: the same tile, its four exchanges (between
+// the stages of either direction and around the Green step) going through LDS
+// as real parts, then imaginary parts.  The pass is bound by the wavefronts in
+// flight: a two-column tile at 240 takes 27 KB of LDS instead of 50, and with
+// the thread's values in registers between the exchanges the kernel needs no
+// scratch, so four workgroups of three wavefronts fit a CU's registers.  For
+// two-stage plans whose stages give a thread at most one butterfly each.
+// Measured, whole tile -> half: FP32 states 240^3 full pass 260 -> 222 us, a
+// hop's pruned one 261 -> 213 (FP64 305 -> 302, 293 -> 244); 160^3 75 -> 71
+// and 76 -> 71 (FP64 80 -> 73, 76 -> 73).  At 256 the whole tile's four
+// wavefronts are as many and its exchanges half as many: 271 -> 255 full, but
+// 230 -> 242 pruned, FP64 353 -> 363, so 256 keeps it.  So does every rotated
+// frame, whose Green step spills here (FP64 160^3 95 -> 120, 240^3 373 -> 492).
+template <int N>
+constexpr bool zg_half() {
+  return N == 160 || N == 240;
+}
+template <int N>
+constexpr int zh_threads() {
+  using FP = FusedPlan<N>;
+  return 12 * (FP::R0 < FP::R1 ? N / FP::R0 : N / FP::R1);
+}
+
+template <int N, typename S, bool PRUNE, bool BATCH = false>
+__global__ __launch_bounds__((zh_threads<N>())) __attribute__((amdgpu_waves_per_eu(3)))
+void k_zgreen_half(typename Cplx<S>::T* __restrict__ spec, Cubic C, Prune pr, const double2* __restrict__ twg,
+                   const HopJob* __restrict__ jobs = nullptr, int njob = 0) {
+  using FP = FusedPlan<N>;
+  constexpr int W = 2, NF = 6 * W;
+  constexpr int R0 = FP::R0, R1 = FP::R1;
+  static_assert(FP::NSTG == 2 && R0 * R1 == N, "two stages");
+  constexpr int T = zh_threads<N>();
+  constexpr int NB0 = NF * (N / R0), NB1 = NF * (N / R1);
+  static_assert(NB0 <= T && NB1 <= T && T % NF == 0, "one butterfly per thread and stage");
+  constexpr int NH = N / 2 + 1;
+  constexpr int KB = (NH + W - 1) / W;
+  constexpr int NT = N * KB;
+  constexpr int NBIN = N * W, BQ = (NBIN + T - 1) / T;
+  constexpr int P = spec_pitch(N, sizeof(S) == 8);
+  constexpr int SI = 6 * N * P;
+  static_assert(6LL * N * N * P < (1LL << 31), "32-bit element offsets");
+  using C2 = typename Cplx<S>::T;
+  __shared__ double buf[NF * N];
+  __shared__ double2 tw[N];
+  const int ntiles = BATCH ? NT * njob : NT;
+  const int per = (ntiles + 7) / 8;
+  const int t = (int)(blockIdx.x % 8) * per + (int)(blockIdx.x / 8);
+  if ((int)(blockIdx.x / 8) >= per || t >= ntiles) return;
+  C2* base = spec;
+  Prune p = pr;
+  int lt = t;
+  if constexpr (BATCH) {
+    const int j = t / NT;
+    base = (C2*)jobs[j].spec;
+    p = Prune{jobs[j].zlo, jobs[j].zlen, 0, N};
+    lt = t - j * NT;
+  }
+  const int ky = lt / KB, kx0 = (lt % KB) * W;
+  // The thread index is laundered in every phase, so that the index arithmetic
+  // is done again there instead of being held in registers: f = tid % NF is the
+  // thread's transform in every stage, j = tid / NF its butterfly.
+  int tid = threadIdx.x;
+  auto launder = [&]() { asm volatile("" : "+v"(tid)); };
+  auto in0 = [&]() { return NB0 == T || tid < NB0; };
+  auto in1 = [&]() { return NB1 == T || tid < NB1; };
+  auto column = [&](bool& valid) -> C2* {
+    const int f = tid % NF;
+    valid = kx0 + f / 6 < NH;
+    return base + (ky * P + (valid ? kx0 : 0)) * 6 + (valid ? f : 0);
+  };
+  // element j R + r (PUT) or j + r M (GET) of the thread's transform
+  auto put = [&](auto& a, auto RC, bool im) {
+    constexpr int R = decltype(RC)::value;
+    launder();
+    double* o = buf + (tid / NF) * (R * NF) + tid % NF;
+#pragma unroll
+    for (int r = 0; r < R; ++r) o[r * NF] = im ? a[r].y : a[r].x;
+  };
+  auto get = [&](auto& a, auto RC, auto MC, bool im) {
+    constexpr int R = decltype(RC)::value, M = decltype(MC)::value;
+    launder();
+    const double* o = buf + tid;  // (tid / NF) NF + tid % NF
+#pragma unroll
+    for (int r = 0; r < R; ++r) (im ? a[r].y : a[r].x) = o[r * (M * NF)];
+  };
+  auto put_at = [&](auto& a, auto RC, auto MC, bool im) {
+    constexpr int R = decltype(RC)::value, M = decltype(MC)::value;
+    launder();
+    double* o = buf + tid;
+#pragma unroll
+    for (int r = 0; r < R; ++r) o[r * (M * NF)] = im ? a[r].y : a[r].x;
+  };
+  using C0 = std::integral_constant<int, R0>;
+  using C1 = std::integral_constant<int, R1>;
+  double2 v[R0], u[R1];
+  if (in0()) {
+    bool valid;
+    const C2* const col = column(valid);
+    const int j = tid / NF;
+#pragma unroll
+    for (int r = 0; r < R0; ++r) {
+      const int i = j + r * (N / R0);
+      bool in = true;
+      if constexpr (PRUNE) {
+        int d = i - p.in_lo;
+        if (d < 0) d += N;
+        in = valid && d < p.in_len;
+      }
+      // planes outside the input range read plane in_lo (a cache hit) and are zeroed
+      const double2 a = ld2(col + (in ? i : p.in_lo) * SI);
+      v[r] = in ? a : make_double2(0.0, 0.0);
+    }
+  }
+  for (int i = threadIdx.x; i < N; i += T) tw[i] = twg[i];
+  if (in0()) {
+    Dft<R0, false>::run(v);
+    put(v, C0{}, false);
+  }
+  __syncthreads();
+  if (in1()) get(u, C1{}, C0{}, false);
+  __syncthreads();
+  if (in0()) put(v, C0{}, true);
+  __syncthreads();
+  if (in1()) {
+    get(u, C1{}, C0{}, true);
+    const int j = tid / NF;
+#pragma unroll
+    for (int r = 1; r < R1; ++r) u[r] = cmul(u[r], tw[j * r]);
+    Dft<R1, false>::run(u);
+  }
+  __syncthreads();
+  // Green step: bins tid + q T of the tile, all six components in registers
+  double2 e[BQ][6];
+  auto bins = [&](auto&& fn) {
+    launder();
+#pragma unroll
+    for (int q = 0; q < BQ; ++q) {
+      const int b = tid + q * T;
+      if (NBIN % T == 0 || b < NBIN) fn(b, e[q]);
+    }
+  };
+  if (in1()) put_at(u, C1{}, C0{}, false);
+  __syncthreads();
+  bins([&](int b, double2* g) {
+#pragma unroll
+    for (int c = 0; c < 6; ++c) g[c].x = buf[6 * b + c];
+  });
+  __syncthreads();
+  if (in1()) put_at(u, C1{}, C0{}, true);
+  __syncthreads();
+  bins([&](int b, double2* g) {
+#pragma unroll
+    for (int c = 0; c < 6; ++c) g[c].y = buf[6 * b + c];
+    const int kx = kx0 + b % W, kz = b / W;
+    __builtin_amdgcn_sched_barrier(0);
+    if (kx < NH) green_bin(g, kx, ky, kz, N, C);
+    __builtin_amdgcn_sched_barrier(0);
+  });
+  __syncthreads();
+  bins([&](int b, double2* g) {
+#pragma unroll
+    for (int c = 0; c < 6; ++c) buf[6 * b + c] = g[c].x;
+  });
+  __syncthreads();
+  if (in1()) get(u, C1{}, C0{}, false);
+  __syncthreads();
+  bins([&](int b, double2* g) {
+#pragma unroll
+    for (int c = 0; c < 6; ++c) buf[6 * b + c] = g[c].y;
+  });
+  __syncthreads();
+  if (in1()) {
+    get(u, C1{}, C0{}, true);
+    Dft<R1, true>::run(u);
+  }
+  __syncthreads();
+  if (in1()) put(u, C1{}, false);
+  __syncthreads();
+  if (in0()) get(v, C0{}, C1{}, false);
+  __syncthreads();
+  if (in1()) put(u, C1{}, true);
+  __syncthreads();
+  if (in0()) {
+    get(v, C0{}, C1{}, true);
+    const int j = tid / NF;
+#pragma unroll
+    for (int r = 1; r < R0; ++r) v[r] = cmul(v[r], conjd(tw[j * r]));
+    Dft<R0, true>::run(v);
+    launder();
+    bool valid;
+    C2* const col = column(valid) + (tid / NF) * SI;
+    if (valid)
+#pragma unroll
+      for (int r = 0; r < R0; ++r) st2(col + r * R1 * SI, v[r]);
+  }
+}
+
 // Pointwise Green step over the half spectrum (one thread per bin).
 template <typename S>
 __global__ __launch_bounds__(256) void k_green(typename Cplx<S>::T* __restrict__ spec, int n, int P, Cubic C) {
@@ -1492,14 +1689,25 @@ hipError_t go_hop_batch(const HopJob* jobs, int njob, SpecGeom g, Cubic C, const
     hipLaunchKernelGGL(k, dim3(grid), dim3(TP), 0, s, (C2*)nullptr, none, tw, 0, (uint32_t*)nullptr, jobs, njob);
   }
   {
-    constexpr int W = zg_width<N, S>();
-    constexpr int T = zg_threads<N, S>();
-    constexpr int NT = N * ((N / 2 + 1 + W - 1) / W);
-    auto* k = C.frm ? k_zgreen<N, S, true, true, true> : k_zgreen<N, S, true, false, true>;
-    bool walk = false;
-    const int grid = zpipe ? walk_grid(k, T, njob * NT, walk) : tile_grid(k, T, njob * NT, false);
-    if (grid < 0) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k, dim3(grid), dim3(T), 0, s, (C2*)nullptr, C, none, tw, walk ? ctr + 8 : nullptr, jobs, njob);
+    bool done = false;
+    if constexpr (zg_half<N>()) {
+      if (!C.frm) {  // the same kernel as a single hop's pass
+        const int nt = njob * N * ((N / 2 + 2) / 2);
+        hipLaunchKernelGGL((k_zgreen_half<N, S, true, true>), dim3(((nt + 7) / 8) * 8), dim3(zh_threads<N>()), 0, s,
+                           (C2*)nullptr, C, none, tw, jobs, njob);
+        done = true;
+      }
+    }
+    if (!done) {
+      constexpr int W = zg_width<N, S>();
+      constexpr int T = zg_threads<N, S>();
+      constexpr int NT = N * ((N / 2 + 1 + W - 1) / W);
+      auto* k = C.frm ? k_zgreen<N, S, true, true, true> : k_zgreen<N, S, true, false, true>;
+      bool walk = false;
+      const int grid = zpipe ? walk_grid(k, T, njob * NT, walk) : tile_grid(k, T, njob * NT, false);
+      if (grid < 0) return hipErrorInvalidValue;
+      hipLaunchKernelGGL(k, dim3(grid), dim3(T), 0, s, (C2*)nullptr, C, none, tw, walk ? ctr + 8 : nullptr, jobs, njob);
+    }
   }
   {
     auto* k = k_pencil<N, S, true, LT, false, 1, true>;
@@ -1639,6 +1847,15 @@ hipError_t go_zgreen(void* spec, SpecGeom g, Cubic C, Prune pr, const double2* t
   using C2 = typename Cplx<S>::T;
   const bool prune = pr.in_len < N;
   if (g.P != spec_pitch(N, sizeof(S) == 8)) return hipErrorInvalidValue;
+  if constexpr (zg_half<N>()) {
+    if (!C.frm) {
+      constexpr int NT = N * ((N / 2 + 2) / 2);
+      auto* k = prune ? k_zgreen_half<N, S, true> : k_zgreen_half<N, S, false>;
+      hipLaunchKernelGGL(k, dim3(((NT + 7) / 8) * 8), dim3(zh_threads<N>()), 0, s, (C2*)spec, C, pr, tw,
+                         (const HopJob*)nullptr, 0);
+      return hipGetLastError();
+    }
+  }
   auto* k = C.frm ? (prune ? k_zgreen<N, S, true, true> : k_zgreen<N, S, false, true>)
                   : (prune ? k_zgreen<N, S, true, false> : k_zgreen<N, S, false, false>);
   bool walk = false;
