@@ -950,7 +950,7 @@ ec_status pipeline(ec_state* st, hipStream_t s, bool fp64, const int32_t* own, c
     const ec_status r = between();
     if (r != EC_OK) return r;
   }
-  LAUNCH(st, s, PF_Z, 2 * sb, launch_z_green(fp64, spec, g, st->C, full, st->tw, ctr ? ctr + 8 : nullptr, s));
+  LAUNCH(st, s, PF_Z, 2 * sb, launch_z_green(fp64, spec, g, st->C, full, st->tw, ctr ? ctr + 8 : nullptr, true, s));
   LAUNCH(st, s, PF_Y, 2 * sb, launch_pencil(fp64, true, 1, spec, g, full, st->tw, ctr ? ctr + 16 : nullptr, s));
   // covered_only: the spectrum and the owner map are read, and the stress is
   // stored at the covered voxels only (their bytes not counted here)
@@ -1795,7 +1795,7 @@ ec_status update_q(ec_state* st, int32_t idx, DevDefect nd, hipStream_t s) {
     const Prune pz{zlo, zlen, 0, n};
     const Prune full{0, n, 0, n};
     LAUNCH(st, s, PF_Z, (1 + frac_z) * sb,
-           launch_z_green(fp64, st->spec, st->g, st->C, pz, st->tw, st->tilectr + 8, s));
+           launch_z_green(fp64, st->spec, st->g, st->C, pz, st->tw, st->tilectr + 8, false, s));
     LAUNCH(st, s, PF_Y, 2 * sb, launch_pencil(fp64, true, 1, st->spec, st->g, full, st->tw, st->tilectr + 16, s));
     LAUNCH(st, s, PF_XI, sb + 2 * fb,
            launch_x_inverse(fp64, true, st->spec, st->sig, st->g, dmean, st->tw, s));

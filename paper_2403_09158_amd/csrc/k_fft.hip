@@ -1148,13 +1148,19 @@ void k_zgreen(typename Cplx<S>::T* __restrict__ spec, Cubic C,
 // two-stage plans whose stages give a thread at most one butterfly each.
 // Measured, whole tile -> half: FP32 states 240^3 full pass 260 -> 222 us, a
 // hop's pruned one 261 -> 213 (FP64 305 -> 302, 293 -> 244); 160^3 75 -> 71
-// and 76 -> 71 (FP64 80 -> 73, 76 -> 73).  At 256 the whole tile's four
-// wavefronts are as many and its exchanges half as many: 271 -> 255 full, but
-// 230 -> 242 pruned, FP64 353 -> 363, so 256 keeps it.  So does every rotated
-// frame, whose Green step spills here (FP64 160^3 95 -> 120, 240^3 373 -> 492).
+// and 76 -> 71 (FP64 80 -> 73, 76 -> 73).  At 256, where the whole tile has four
+// wavefronts a workgroup and needs no scratch either, only the solves of FP32
+// states gain (271 -> 255): hops 230 -> 242 and FP64 353 -> 363, so these keep
+// it (a hop by its caller, not by its planes, so that a batched hop and a single
+// one of any extent run the same kernel).  So does every rotated frame, whose
+// Green step spills here (FP64 160^3 95 -> 120, 240^3 373 -> 492).
 template <int N>
 constexpr bool zg_half() {
   return N == 160 || N == 240;
+}
+template <int N, typename S>
+constexpr bool zg_half_solve() {
+  return zg_half<N>() || (N == 256 && sizeof(S) == 4);
 }
 template <int N>
 constexpr int zh_threads() {
@@ -1840,21 +1846,24 @@ hipError_t launch_green(bool fp64, void* spec, SpecGeom g, Cubic C, hipStream_t 
 }
 
 template <int N, typename S>
-hipError_t go_zgreen(void* spec, SpecGeom g, Cubic C, Prune pr, const double2* tw, uint32_t* ctr, hipStream_t s) {
+hipError_t go_zgreen(void* spec, SpecGeom g, Cubic C, Prune pr, const double2* tw, uint32_t* ctr, bool solve,
+                     hipStream_t s) {
   constexpr int W = zg_width<N, S>();
   constexpr int T = zg_threads<N, S>();
   constexpr int NT = N * ((N / 2 + 1 + W - 1) / W);
   using C2 = typename Cplx<S>::T;
   const bool prune = pr.in_len < N;
   if (g.P != spec_pitch(N, sizeof(S) == 8)) return hipErrorInvalidValue;
+  auto half = [&](auto* k) {
+    constexpr int NTH = N * ((N / 2 + 2) / 2);
+    hipLaunchKernelGGL(k, dim3(((NTH + 7) / 8) * 8), dim3(zh_threads<N>()), 0, s, (C2*)spec, C, pr, tw,
+                       (const HopJob*)nullptr, 0);
+    return hipGetLastError();
+  };
   if constexpr (zg_half<N>()) {
-    if (!C.frm) {
-      constexpr int NT = N * ((N / 2 + 2) / 2);
-      auto* k = prune ? k_zgreen_half<N, S, true> : k_zgreen_half<N, S, false>;
-      hipLaunchKernelGGL(k, dim3(((NT + 7) / 8) * 8), dim3(zh_threads<N>()), 0, s, (C2*)spec, C, pr, tw,
-                         (const HopJob*)nullptr, 0);
-      return hipGetLastError();
-    }
+    if (!C.frm) return half(prune ? k_zgreen_half<N, S, true> : k_zgreen_half<N, S, false>);
+  } else if constexpr (zg_half_solve<N, S>()) {
+    if (!C.frm && solve && !prune) return half(k_zgreen_half<N, S, false>);
   }
   auto* k = C.frm ? (prune ? k_zgreen<N, S, true, true> : k_zgreen<N, S, false, true>)
                   : (prune ? k_zgreen<N, S, true, false> : k_zgreen<N, S, false, false>);
@@ -1867,12 +1876,12 @@ hipError_t go_zgreen(void* spec, SpecGeom g, Cubic C, Prune pr, const double2* t
 }
 
 hipError_t launch_z_green(bool fp64, void* spec, SpecGeom g, Cubic C, Prune pr, const double2* tw, uint32_t* ctr,
-                          hipStream_t s) {
+                          bool solve, hipStream_t s) {
   switch (g.n) {
 #define EC_CASE(NN)                                                      \
   case NN:                                                               \
-    return fp64 ? go_zgreen<NN, double>(spec, g, C, pr, tw, ctr, s)      \
-                : go_zgreen<NN, float>(spec, g, C, pr, tw, ctr, s);
+    return fp64 ? go_zgreen<NN, double>(spec, g, C, pr, tw, ctr, solve, s)      \
+                : go_zgreen<NN, float>(spec, g, C, pr, tw, ctr, solve, s);
     EC_FOR_SIZES(EC_CASE)
 #undef EC_CASE
   }
