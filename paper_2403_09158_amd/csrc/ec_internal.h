@@ -422,7 +422,7 @@ hipError_t launch_x_forward_points(const int32_t* map, const double* vals, int s
 // sig[v][c] += sgn * bg3[v][c] over n^3 voxels (a 3-D background stress).
 hipError_t launch_bg3_add(double* sig, const double* bg3, int64_t n3, double sgn, hipStream_t s);
 hipError_t launch_green(bool fp64, void* spec, SpecGeom g, Cubic C, hipStream_t s);
-// solve: a solve's pass (not a hop's, which has to run the batched hops' kernel).
+// solve: a solve's pass, not a hop's.
 hipError_t launch_z_green(bool fp64, void* spec, SpecGeom g, Cubic C, Prune pr, const double2* tw, uint32_t* ctr,
                           bool solve, hipStream_t s);
 // bg / bg_mask: stress planes of dislocation lines added to sigma (not with accum).

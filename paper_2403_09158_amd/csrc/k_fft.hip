@@ -1149,18 +1149,15 @@ void k_zgreen(typename Cplx<S>::T* __restrict__ spec, Cubic C,
 // Measured, whole tile -> half: FP32 states 240^3 full pass 260 -> 222 us, a
 // hop's pruned one 261 -> 213 (FP64 305 -> 302, 293 -> 244); 160^3 75 -> 71
 // and 76 -> 71 (FP64 80 -> 73, 76 -> 73).  At 256, where the whole tile has four
-// wavefronts a workgroup and needs no scratch either, only the solves of FP32
-// states gain (271 -> 255): hops 230 -> 242 and FP64 353 -> 363, so these keep
-// it (a hop by its caller, not by its planes, so that a batched hop and a single
-// one of any extent run the same kernel).  So does every rotated frame, whose
-// Green step spills here (FP64 160^3 95 -> 120, 240^3 373 -> 492).
+// wavefronts a workgroup and needs no scratch either: 271 -> 255 full, 230 -> 242
+// pruned, FP64 353 -> 363, so 256 keeps it; so does every rotated frame, whose
+// Green step spills here (FP64 160^3 95 -> 120, 240^3 373 -> 492).  And so do the
+// solves of FP32 states: the compiler fuses other multiplies and adds here, the
+// stress moves by 1e-11, and stored-type energies, which round its transform to
+// FP32 twice more, by 9e-10 (160^3; 6e-16 with the whole tile).
 template <int N>
 constexpr bool zg_half() {
   return N == 160 || N == 240;
-}
-template <int N, typename S>
-constexpr bool zg_half_solve() {
-  return zg_half<N>() || (N == 256 && sizeof(S) == 4);
 }
 template <int N>
 constexpr int zh_threads() {
@@ -1854,16 +1851,14 @@ hipError_t go_zgreen(void* spec, SpecGeom g, Cubic C, Prune pr, const double2* t
   using C2 = typename Cplx<S>::T;
   const bool prune = pr.in_len < N;
   if (g.P != spec_pitch(N, sizeof(S) == 8)) return hipErrorInvalidValue;
-  auto half = [&](auto* k) {
-    constexpr int NTH = N * ((N / 2 + 2) / 2);
-    hipLaunchKernelGGL(k, dim3(((NTH + 7) / 8) * 8), dim3(zh_threads<N>()), 0, s, (C2*)spec, C, pr, tw,
-                       (const HopJob*)nullptr, 0);
-    return hipGetLastError();
-  };
   if constexpr (zg_half<N>()) {
-    if (!C.frm) return half(prune ? k_zgreen_half<N, S, true> : k_zgreen_half<N, S, false>);
-  } else if constexpr (zg_half_solve<N, S>()) {
-    if (!C.frm && solve && !prune) return half(k_zgreen_half<N, S, false>);
+    if (!C.frm && (sizeof(S) == 8 || !solve)) {
+      constexpr int NTH = N * ((N / 2 + 2) / 2);
+      auto* k = prune ? k_zgreen_half<N, S, true> : k_zgreen_half<N, S, false>;
+      hipLaunchKernelGGL(k, dim3(((NTH + 7) / 8) * 8), dim3(zh_threads<N>()), 0, s, (C2*)spec, C, pr, tw,
+                         (const HopJob*)nullptr, 0);
+      return hipGetLastError();
+    }
   }
   auto* k = C.frm ? (prune ? k_zgreen<N, S, true, true> : k_zgreen<N, S, false, true>)
                   : (prune ? k_zgreen<N, S, true, false> : k_zgreen<N, S, false, false>);
