@@ -1517,8 +1517,13 @@ double list_volume(const DevDefect* h, int ndef) {
 // part of the cell.
 bool sparse_rows(const ec_state* st) { return st->fp64 && st->volume < rows_limit(st->n) * (double)st->n3; }
 
-// Cells up to which the self terms go before the passes (solve_table).
+// Cells and lists up to which the self terms go before the passes (solve_table).
+// The classes are then assigned on the host before the first launch (about 10 ns
+// a defect, none of it hidden), which pays while the x and y passes are too short
+// to hide the self terms: FP64 96^3, 600 defects 219 us early against 227, 1000
+// defects 249 against 245; 128^3, 1000 defects 312 against 294, 2500 449 against 402.
 constexpr int64_t EARLY_SELF_VOXELS = 128 * 128 * 128;
+constexpr int64_t EARLY_SELF_WORK = 700LL * 1000 * 1000;  // defects x voxels: 800 defects at 96^3
 
 // Commits the quantised list h (ndef entries in the pinned staging buffer of
 // the device table, pin_begin already called on it) and solves: footprint
@@ -1554,7 +1559,8 @@ ec_status solve_table(ec_state* st, DevDefect* h, int32_t ndef, hipStream_t s, b
   // are queued before them, with the classes already in the uploaded table, and
   // only what follows the solve waits for them (on larger cells the classes are
   // assigned while the passes run, and the z pass waits, see below)
-  const bool early = h && ndef > 0 && !keep_self && st->n3 <= EARLY_SELF_VOXELS;
+  const bool early = h && ndef > 0 && !keep_self && st->n3 <= EARLY_SELF_VOXELS &&
+                     (int64_t)ndef * st->n3 <= EARLY_SELF_WORK;
   std::vector<DevDefect> list;
   if (early) {
     list.assign(h, h + ndef);
