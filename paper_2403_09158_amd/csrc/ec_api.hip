@@ -1278,6 +1278,14 @@ ec_status compute_self_terms(ec_state* st, hipStream_t s) {
   return EC_OK;
 }
 
+// Whether stream s is being captured.
+ec_status under_capture(hipStream_t s, bool& yes) {
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (s) HIPCHK(hipStreamIsCapturing(s, &cs));
+  yes = cs != hipStreamCaptureStatusNone;
+  return EC_OK;
+}
+
 // Polls an event.
 ec_status wait_event(hipEvent_t ev) {
   hipError_t q;
@@ -1289,28 +1297,31 @@ ec_status wait_event(hipEvent_t ev) {
 
 // Make stream s wait for self terms still running on the side stream.  Terms
 // that have ended need no wait in the stream (which costs it some ten
-// microseconds).  A stream under capture cannot wait for work outside the
-// capture, so there the host waits for them, in the capture mode that allows it
-// to ask.
+// microseconds).  Their event is asked for in the capture mode that allows it,
+// since the calling thread may be capturing s or a stream of its own.  A stream
+// under capture cannot wait for work outside the capture, so there the host
+// waits for the terms.
 ec_status join_self(ec_state* st, hipStream_t s) {
   if (!st->self_pending) return EC_OK;
-  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-  if (s) HIPCHK(hipStreamIsCapturing(s, &cs));
-  if (cs != hipStreamCaptureStatusNone) {
-    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-    HIPCHK(hipThreadExchangeStreamCaptureMode(&mode));
-    const ec_status r = wait_event(st->ev_self);
-    HIPCHK(hipThreadExchangeStreamCaptureMode(&mode));
-    if (r != EC_OK) return r;
-  } else {
+  bool captured = false;
+  ec_status r = under_capture(s, captured);
+  if (r != EC_OK) return r;
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  HIPCHK(hipThreadExchangeStreamCaptureMode(&mode));
+  auto join = [&]() -> ec_status {
+    if (captured) return wait_event(st->ev_self);
     const hipError_t q = hipEventQuery(st->ev_self);
-    if (q == hipErrorNotReady)
-      HIPCHK(hipStreamWaitEvent(s, st->ev_self, 0));
-    else
+    if (q != hipErrorNotReady) {
       HIPCHK(q);
-  }
-  st->self_pending = false;
-  return EC_OK;
+      return EC_OK;
+    }
+    HIPCHK(hipStreamWaitEvent(s, st->ev_self, 0));
+    return EC_OK;
+  };
+  r = join();
+  HIPCHK(hipThreadExchangeStreamCaptureMode(&mode));
+  if (r == EC_OK) st->self_pending = false;
+  return r;
 }
 
 // Self terms of the list just rasterised on stream s, computed on the side

@@ -1,0 +1,49 @@
+"""Calls while the calling thread captures a stream: the energies of a state on
+another stream, asked for while its self terms may still run beside its solve,
+do not disturb the capture."""
+import numpy as np
+import pytest
+
+from paper_2403_09158_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+
+def _solved(stream, n=64, ndef=200):
+    from paper_2403_09158_amd import ec
+
+    h = inputs.H_VOXEL
+    d = inputs.mixed_population(np.random.default_rng(9), ndef, n * h, h, r111=(0.5, 5.0), r100=(1.0, 6.0))
+    st = ec.State(ec.Context(), inputs.Problem(n, n * h, *inputs.CUBIC_FE, prec=1))
+    st.solve(d, stream=stream)
+    return st, d, st.energies(stream=stream)
+
+
+def _replayed(g, x):
+    import torch
+
+    for _ in range(3):
+        x.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert float(x.sum()) == 4.0
+
+
+@pytest.mark.parametrize("mode", ["relaxed", "thread_local", "global"])
+def test_energies_on_another_stream(mode):
+    import torch
+
+    s, other = torch.cuda.Stream(), torch.cuda.Stream()
+    st, d, ref = _solved(other)
+    out = torch.zeros(len(d), dtype=torch.float64, device="cuda")
+    x = torch.zeros(4, device="cuda")
+    g = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    st.solve(d, stream=other)
+    with torch.cuda.graph(g, stream=s, capture_error_mode=mode):
+        x.add_(1.0)
+        st.energies(stream=other, out=out)
+    torch.cuda.synchronize()
+    assert np.array_equal(out.cpu().numpy(), ref)
+    _replayed(g, x)
+    st.close()
