@@ -163,7 +163,9 @@ EC_API ec_status ec_state_bytes(const ec_state* st, size_t* bytes);
  * stored-type energies), on that call's stream.
  * Optional outputs eps_out / sig_out ([6][n^3], float for EC_FP32 states,
  * double for EC_FP64 states) on the device (out_on_device != 0) or on the host;
- * NULL skips them.  Replaces any previous defect list of the state. */
+ * NULL skips them.  Replaces any previous defect list of the state.
+ * A solve of a list cannot be part of a HIP graph: on a stream under capture
+ * the call fails (EC_ERR_DEVICE) and leaves the state and the capture alone. */
 EC_API ec_status ec_solve_fields(ec_state* st, const ec_defect* defs, int32_t ndef, void* hip_stream, void* eps_out,
                           void* sig_out, int32_t out_on_device);
 

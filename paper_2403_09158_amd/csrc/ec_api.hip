@@ -1300,7 +1300,7 @@ ec_status wait_event(hipEvent_t ev) {
 // microseconds).  Their event is asked for in the capture mode that allows it,
 // since the calling thread may be capturing s or a stream of its own.  A stream
 // under capture cannot wait for work outside the capture, so there the host
-// waits for the terms.
+// waits for the terms (never part of a capture: a solve refuses one).
 ec_status join_self(ec_state* st, hipStream_t s) {
   if (!st->self_pending) return EC_OK;
   bool captured = false;
@@ -2193,9 +2193,14 @@ ec_status ec_solve_fields(ec_state* st, const ec_defect* defs, int32_t ndef, voi
   if (!st) return fail(EC_ERR_ARG, "state is NULL");
   if (ndef < 0 || (ndef > 0 && !defs)) return fail(EC_ERR_ARG, "bad defect array");
   hipStream_t s = (hipStream_t)stream;
+  // a capture would record the list's upload from staging memory that later
+  // solves rewrite, and work on the side stream that outlasts the call
+  bool captured = false;
+  ec_status r = under_capture(s, captured);
+  if (r != EC_OK) return r;
+  if (captured && ndef > 0) return fail(EC_ERR_DEVICE, "a solve cannot be part of a stream capture");
   // validate and quantise everything before touching the state, straight into
   // the pinned staging buffer of the device table
-  ec_status r;
   char* hp = nullptr;
   if ((r = pin_begin(st->pin_tab, std::max<size_t>(ndef, 1) * sizeof(DevDefect), &hp)) != EC_OK) return r;
   DevDefect* h = (DevDefect*)hp;

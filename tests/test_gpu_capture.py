@@ -1,6 +1,7 @@
 """Calls while the calling thread captures a stream: the energies of a state on
 another stream, asked for while its self terms may still run beside its solve,
-do not disturb the capture."""
+do not disturb the capture; a solve on the captured stream is refused and leaves
+the state, and the capture, as they were."""
 import numpy as np
 import pytest
 
@@ -46,4 +47,26 @@ def test_energies_on_another_stream(mode):
     torch.cuda.synchronize()
     assert np.array_equal(out.cpu().numpy(), ref)
     _replayed(g, x)
+    st.close()
+
+
+@pytest.mark.parametrize("n, ndef", [(64, 200), (160, 50)])
+def test_solve_is_refused(n, ndef):
+    import torch
+
+    from paper_2403_09158_amd import ec
+
+    s, other = torch.cuda.Stream(), torch.cuda.Stream()
+    st, d, ref = _solved(other, n, ndef)
+    x = torch.zeros(4, device="cuda")
+    g = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(g, stream=s, capture_error_mode="relaxed"):
+        x.add_(1.0)
+        with pytest.raises(ec.EcError):
+            st.solve(d[: ndef // 2], stream=s)
+    _replayed(g, x)
+    assert np.array_equal(st.energies(stream=other), ref)
+    st.solve(d, stream=other)
+    assert np.array_equal(st.energies(stream=other), ref)
     st.close()
