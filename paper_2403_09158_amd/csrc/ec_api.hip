@@ -2223,7 +2223,11 @@ ec_status ec_solve_fields(ec_state* st, const ec_defect* defs, int32_t ndef, voi
       if (bad[c] != INT_MAX) return fail(EC_ERR_ARG, "defect %d: %s", bad[c], why[c].c_str());
   }
   if ((r = solve_table(st, h, ndef, s)) != EC_OK) return r;
-  if (eps_out && sig_out && on_device) {  // both from one pass over the stress
+  // both from one pass over the stress, where neither output lies in the other
+  // (else the stress is written after the strain, over it)
+  const uintptr_t eo = (uintptr_t)eps_out, so = (uintptr_t)sig_out;
+  const uintptr_t fb = (uintptr_t)6 * st->n3 * (st->fp64 ? 8 : 4);
+  if (eps_out && sig_out && on_device && (eo + fb <= so || so + fb <= eo)) {
     if ((r = ensure_sigma(st, s)) != EC_OK) return r;
     const DefBuf& b = st->db[st->cur];
     LAUNCH(st, s, PF_OTHER, (st->fp64 ? 144.0 : 96.0) * st->n3,
