@@ -1590,7 +1590,8 @@ ec_status solve_table(ec_state* st, DevDefect* h, int32_t ndef, hipStream_t s, b
   }
   // commit: remove the old eigenstrain, add the new one
   if ((r = join_self(st, s)) != EC_OK) return r;
-  // a list moved on the device keeps its shapes and so its volume
+  // a list moved on the device keeps its shapes and so its volume (update_q
+  // renews it where a move changes a shape)
   if (h) st->volume = list_volume(h, ndef);
   const DefBuf& ob = st->db[st->cur];
   if (st->ndef > 0)
@@ -1832,6 +1833,7 @@ ec_status update_q(ec_state* st, int32_t idx, DevDefect nd, hipStream_t s) {
     if (st->classes.size() != ncls_before) st->gcls_ncls = -1;
   }
   st->hdefs[idx] = nd;
+  if (!hop) st->volume = list_volume(st->hdefs.data(), st->ndef);
   return EC_OK;
 }
 
