@@ -411,11 +411,17 @@ namespace {
 
 // ------------------------------------------------------------------ memory / ledger
 
+// NULL when the device memory is not to be had; the runtime's error is taken
+// back then, or the next launch (of this call's other route, or of a later call)
+// would report it.
 void* raw_alloc(ec_ctx* c, size_t bytes) {
   if (bytes == 0) bytes = 64;
-  if (c->af) return c->af(bytes, nullptr, c->user);
   void* p = nullptr;
-  if (hipMalloc(&p, bytes) != hipSuccess) return nullptr;
+  if (c->af)
+    p = c->af(bytes, nullptr, c->user);
+  else if (hipMalloc(&p, bytes) != hipSuccess)
+    p = nullptr;
+  if (!p) (void)hipGetLastError();
   return p;
 }
 
