@@ -184,51 +184,57 @@ __device__ __forceinline__ int shift_id(int id, int sx, int sy, int sz, int n) {
   return (z * n + y) * n + x;
 }
 
-// A moved defect taken from the chains of its old voxels, then put on those of
-// its new ones (ids shifted in place, or copied from new_ids), and its record
-// renewed.  Each voxel of one footprint is visited by exactly one thread, and no
-// other chain changes meanwhile.  The defect sits on a chain either as a
+// Takes defect `def` out of the chain of voxel id.  It sits there either as a
 // terminal id or as an entry; either way the link that points to it is
-// redirected past it.  One workgroup: a footprint takes a few steps of it, and
-// its barrier orders the two halves, which as two launches of sixteen
-// workgroups took 4.5 us each with the gap between them.
-constexpr int MVT = 1024;
-
-__global__ __launch_bounds__(MVT) void k_move_lists(int def, int max_links, int32_t* __restrict__ cnt_p, int64_t slot,
-                                                    const int32_t* __restrict__ new_ids, int cnt_new, int sx, int sy,
-                                                    int sz, int n, int32_t* ids, int2* lnk, int32_t* own,
-                                                    DevDefect* __restrict__ tab, DevDefect rec) {
-  const int old_cnt = cnt_p[def];
-  for (int k = threadIdx.x; k < old_cnt; k += MVT) {
-    int32_t* p = &own[ids[slot + k]];
-    for (int guard = 0; guard < max_links; ++guard) {  // a chain holds each defect once
-      const int32_t link = *p;
-      if (link == -1) break;  // not found (cannot happen for a consistent chain)
-      if (link >= 0) {
-        if (link == def) *p = -1;
-        break;
-      }
-      int2* L = &lnk[-2 - link];
-      if (L->x == def) {
-        *p = L->y;
-        break;
-      }
-      p = &L->y;
+// redirected past it.  Each voxel of one footprint is visited by exactly one
+// thread, and no other chain changes meanwhile.
+__device__ __forceinline__ void unlink_voxel(int def, int max_links, int id, int2* lnk, int32_t* own) {
+  int32_t* p = &own[id];
+  for (int guard = 0; guard < max_links; ++guard) {  // a chain holds each defect once
+    const int32_t link = *p;
+    if (link == -1) break;
+    if (link >= 0) {
+      if (link == def) *p = -1;
+      break;
     }
+    int2* L = &lnk[-2 - link];
+    if (L->x == def) {
+      *p = L->y;
+      break;
+    }
+    p = &L->y;
   }
-  __threadfence();
-  __syncthreads();
-  const int cnt = new_ids ? cnt_new : old_cnt;
-  for (int k = threadIdx.x; k < cnt; k += MVT) {
-    const int64_t e = rec.slot + k;
-    const int id = new_ids ? new_ids[k] : shift_id(ids[slot + k], sx, sy, sz, n);
-    ids[e] = id;
-    int32_t next = -1;
-    if (atomicCAS(&own[id], -1, def) != -1) next = atomicExch(&own[id], entry_link(e));
-    lnk[e] = make_int2(def, next);
-  }
-  if (threadIdx.x == 0) {
-    if (new_ids) cnt_p[def] = cnt;
+}
+
+// Puts defect `def` on the chain of voxel id, as entry e where it is not the first.
+__device__ __forceinline__ void link_voxel(int def, int id, int64_t e, int32_t* ids, int2* lnk, int32_t* own) {
+  ids[e] = id;
+  int32_t next = -1;
+  if (atomicCAS(&own[id], -1, def) != -1) next = atomicExch(&own[id], entry_link(e));
+  lnk[e] = make_int2(def, next);
+}
+
+// A moved defect taken from the chains of its old voxels; then, a second launch,
+// put on those of its new ones (ids shifted in place, or copied from new_ids)
+// and its record renewed.  Two launches of sixteen workgroups: one workgroup for
+// both, ordered by its barrier, takes 3 to 4 us more for a handful of voxels
+// (64^3 hop 55.5 us against 59 at 33 voxels) and 0.3 ms more for 2 10^5 (128^3).
+__global__ __launch_bounds__(RT) void k_unlink(int def, int max_links, const int32_t* __restrict__ cnt_p, int64_t slot,
+                                               const int32_t* __restrict__ ids, int2* lnk, int32_t* own) {
+  const int cnt = cnt_p[def];
+  for (int k = blockIdx.x * RT + threadIdx.x; k < cnt; k += gridDim.x * RT)
+    unlink_voxel(def, max_links, ids[slot + k], lnk, own);
+}
+
+__global__ __launch_bounds__(RT) void k_link(int def, int32_t* cnt_p, int64_t slot,
+                                             const int32_t* __restrict__ new_ids, int cnt_new, int sx, int sy, int sz,
+                                             int n, int32_t* ids, int2* lnk, int32_t* own, DevDefect* __restrict__ tab,
+                                             DevDefect rec) {
+  const int cnt = new_ids ? cnt_new : cnt_p[def];
+  for (int k = blockIdx.x * RT + threadIdx.x; k < cnt; k += gridDim.x * RT)
+    link_voxel(def, new_ids ? new_ids[k] : shift_id(ids[slot + k], sx, sy, sz, n), rec.slot + k, ids, lnk, own);
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    if (new_ids) cnt_p[def] = cnt;  // no workgroup reads the count then
     tab[def] = rec;
   }
 }
@@ -238,39 +244,16 @@ __global__ __launch_bounds__(MVT) void k_move_lists(int def, int max_links, int3
 // job's moved record into its table.  Sixteen blocks per job.
 __global__ __launch_bounds__(RT) void k_unlink_batch(const HopJob* __restrict__ jobs) {
   const HopJob& J = jobs[blockIdx.x / 16];
-  const int lb = blockIdx.x % 16;
   const int cnt = J.cnt[J.idx];
-  for (int k = lb * RT + threadIdx.x; k < cnt; k += 16 * RT) {
-    int32_t* p = &J.own[J.ids[J.slot + k]];
-    for (int guard = 0; guard < J.ndef; ++guard) {  // a chain holds each defect once
-      const int32_t link = *p;
-      if (link == -1) break;
-      if (link >= 0) {
-        if (link == J.idx) *p = -1;
-        break;
-      }
-      int2* L = &J.lnk[-2 - link];
-      if (L->x == J.idx) {
-        *p = L->y;
-        break;
-      }
-      p = &L->y;
-    }
-  }
+  for (int k = (blockIdx.x % 16) * RT + threadIdx.x; k < cnt; k += 16 * RT)
+    unlink_voxel(J.idx, J.ndef, J.ids[J.slot + k], J.lnk, J.own);
 }
 
 __global__ __launch_bounds__(RT) void k_link_batch(const HopJob* __restrict__ jobs, int n) {
   const HopJob& J = jobs[blockIdx.x / 16];
-  const int lb = blockIdx.x % 16;
   const int cnt = J.cnt[J.idx];
-  for (int k = lb * RT + threadIdx.x; k < cnt; k += 16 * RT) {
-    const int64_t e = J.slot + k;
-    const int id = shift_id(J.ids[e], J.sx, J.sy, J.sz, n);
-    J.ids[e] = id;
-    int32_t next = -1;
-    if (atomicCAS(&J.own[id], -1, J.idx) != -1) next = atomicExch(&J.own[id], entry_link(e));
-    J.lnk[e] = make_int2(J.idx, next);
-  }
+  for (int k = (blockIdx.x % 16) * RT + threadIdx.x; k < cnt; k += 16 * RT)
+    link_voxel(J.idx, shift_id(J.ids[J.slot + k], J.sx, J.sy, J.sz, n), J.slot + k, J.ids, J.lnk, J.own);
 }
 
 __global__ __launch_bounds__(64) void k_set_records(const HopJob* __restrict__ jobs) {
@@ -384,8 +367,11 @@ hipError_t launch_unraster(const DevDefect* d, int ndef, const int32_t* counts, 
 hipError_t launch_move_lists(int def, int ndef, int32_t* cnt, int64_t old_slot, const int32_t* new_ids, int cnt_new,
                              int shift_x, int shift_y, int shift_z, int n, int32_t* ids, int2* lnk, int32_t* own,
                              DevDefect* tab, const DevDefect& rec, hipStream_t s) {
-  hipLaunchKernelGGL(k_move_lists, dim3(1), dim3(MVT), 0, s, def, ndef, cnt, old_slot, new_ids, cnt_new, shift_x,
-                     shift_y, shift_z, n, ids, lnk, own, tab, rec);
+  hipLaunchKernelGGL(k_unlink, dim3(16), dim3(RT), 0, s, def, ndef, cnt, old_slot, ids, lnk, own);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_link, dim3(16), dim3(RT), 0, s, def, cnt, old_slot, new_ids, cnt_new, shift_x, shift_y,
+                     shift_z, n, ids, lnk, own, tab, rec);
   return hipGetLastError();
 }
 
