@@ -209,11 +209,16 @@ __global__ __launch_bounds__(256) void k_type_finish(const double* __restrict__ 
 
 }  // namespace
 
-// kz planes per workgroup: long enough to amortise the column phases, short
-// enough for about a thousand workgroups.
+// kz planes per workgroup: eight amortise the column phases (more where a
+// thousand workgroups have more), but a plane is a round trip to memory, so
+// cells with fewer than 128 such workgroups split into pieces of two planes up.
+// us per call, eight planes / this: 32^3 FP64, 1 position 92 / 84, 16 positions
+// 114 / 97; 48^3 98 / 89 and 116 / 100; 64^3 106 / 101 and 129 / 118.  Eight stay
+// from 96^3 on (FP64, 16 positions: 155, with four planes 159).
 static int type_chunk(int n) {
   const int ncol = (n * (n / 2 + 1) + TT - 1) / TT;
-  return std::max(8, (n * ncol + 1023) / 1024);
+  const int few = std::min(8, std::max(2, (n * ncol + 127) / 128));
+  return std::max(few, (n * ncol + 1023) / 1024);
 }
 
 int type_energy_grid(int n) {
