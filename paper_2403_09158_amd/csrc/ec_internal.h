@@ -335,6 +335,8 @@ struct Prune {
 };
 
 bool fft_supported(int n);
+// Whether the transforms of length n hold a direct radix (fft_core.h).
+bool direct_length(int n);
 int pencil_width(int n, bool fp64);
 
 // Tile counters of the persistent passes (eight per pass, one per XCD; the

@@ -322,7 +322,7 @@ __device__ __forceinline__ double2 twiddle(const TwReg<R>& t, int r, int) {
 // workgroup's threads share them out (up to seven each, three output pairs of a
 // length-43 butterfly per thread) instead of leaving most threads idle (x inverse
 // pass: 27 butterflies for 256 threads).  129^3 solves, us before / now: FP32 762
-// / 559, FP64 849 / 523.
+// / 525, FP64 849 / 560.
 constexpr int direct_split(int nb, int threads) { return nb >= threads ? 1 : (threads / nb < 7 ? threads / nb : 7); }
 
 // One Stockham stage over `nfft` transforms of length N with radix R after
@@ -559,8 +559,9 @@ constexpr bool half_plan() {
 // Two-stage transform whose exchange goes through LDS in two halves, the real
 // parts and then the imaginary parts, so that it takes half the LDS of an
 // exchange of complex values (and more workgroups fit a CU) for two more
-// barriers.  at(f, i): the LDS entry of element i of transform f.  The values
-// are those of transform().
+// barriers.  at(f, i): the LDS entry of element i of transform f.  The operations
+// are those of transform(); which multiplies and adds the compiler fuses can
+// differ from kernel to kernel, so two kernels agree to rounding only.
 template <int N, bool INV, Map M, int NFFT, int T, class TW, class Load0, class At, class StoreLast>
 __device__ __forceinline__ void transform_half(const TW& tw, Load0&& load0, At&& at, StoreLast&& store_last) {
   constexpr Plan2 P = plan_of(N);

@@ -1148,7 +1148,9 @@ void k_zgreen(typename Cplx<S>::T* __restrict__ spec, Cubic C,
 // two-stage plans whose stages give a thread at most one butterfly each.
 // Measured, whole tile -> half: FP32 states 240^3 full pass 260 -> 222 us, a
 // hop's pruned one 261 -> 213 (FP64 305 -> 302, 293 -> 244); 160^3 75 -> 71
-// and 76 -> 71 (FP64 80 -> 73, 76 -> 73).  At 256, where the whole tile has four
+// and 76 -> 71 (FP64 80 -> 73, 76 -> 73).  Below, there is little to gain (48^3
+// 13.7 -> 10.4, 64^3 15.7 -> 14.0, 96^3 28.4 -> 27.4) or a loss (128^3 41 -> 44),
+// so 24 to 128 keep the whole tile.  At 256, where the whole tile has four
 // wavefronts a workgroup and needs no scratch either: 271 -> 255 full, 230 -> 242
 // pruned, FP64 353 -> 363, so 256 keeps it; so does every rotated frame, whose
 // Green step spills here (FP64 160^3 95 -> 120, 240^3 373 -> 492).  And so do the
@@ -1741,6 +1743,8 @@ bool fft_supported(int n) {
   }
 }
 
+bool direct_length(int n) { return has_direct(plan_of(n)); }
+
 // Up to this part of the cell's voxels the direct row sums of the x forward
 // pass beat its transforms.  The sums cost a fixed share per covered voxel, the
 // transforms nothing more: us for the pass with rows / with transforms, at 0.5,
@@ -1748,7 +1752,7 @@ bool fft_supported(int n) {
 // 240^3 204 / 225; past that the transforms win (6.4 % of 160^3: 65 / 61, 21 %
 // of 128^3: 50 / 42).  Where the transform has a direct large radix the sums win
 // by far (129^3: 21 / 171 at 0.6 %, 32 / 175 at 5 %).
-double rows_limit(int n) { return n == 129 ? 0.5 : 0.04; }
+double rows_limit(int n) { return direct_length(n) ? 0.5 : 0.04; }
 
 int pencil_width(int n, bool) { return n >= 512 ? 8 : 16; }
 
@@ -2065,17 +2069,11 @@ __global__ __launch_bounds__(256) void k_bg_add(double* __restrict__ sig, const 
   for (int c = 0; c < 6; ++c) q[c] += sgn * add[c];
 }
 
-// Dislocation paths in any direction (Sec. 3.1): per bin of the half spectrum
-// the Nye tensor alpha_hat_il = sum over pieces of M_il rho_hat, with the
-// trilinear spread of a piece separable per axis,
-//   rho_hat = prod_a e^{-2 pi i k_a f_a / n} ((1 - fr_a) + fr_a e^{-2 pi i k_a / n}),
-// the exponents reduced exactly (k_a f_a mod n) and read from the twiddle
-// table; then U_hat_ij = -i e_jkl xi_k alpha_hat_il / |xi|^2 (at an even n's
-// Nyquist bins the mean over the all -n/2 and all +n/2 representatives),
-// eps*_hat = sym(U_hat) and the Green step.  Pieces are staged in LDS in
-// chunks; one thread per bin.
-// sigma_hat (in e) of a bin from the nine components of its Nye tensor spectrum:
-// the distortion operator (Nyquist mean), sym(U), the Green step; zero at xi = 0.
+// Dislocation paths in any direction (Sec. 3.1): sigma_hat (in e) of a bin of the
+// half spectrum from the nine components alpha_hat_il of its Nye tensor,
+// U_hat_ij = -i e_jkl xi_k alpha_hat_il / |xi|^2 (at an even n's Nyquist bins the
+// mean over the all -n/2 and all +n/2 representatives), eps*_hat = sym(U_hat) and
+// the Green step; zero at xi = 0.
 __device__ __forceinline__ void path_bin(const double2* al, int kx, int ky, int kz, int n, double L, const Cubic& C,
                                          double2* e) {
 #pragma unroll
@@ -2127,6 +2125,11 @@ __device__ __forceinline__ void path_bin(const double2* al, int kx, int ky, int 
   }
 }
 
+// alpha_hat summed over the pieces at every bin, sum of M_il rho_hat with the
+// trilinear spread of a piece separable per axis,
+//   rho_hat = prod_a e^{-2 pi i k_a f_a / n} ((1 - fr_a) + fr_a e^{-2 pi i k_a / n}),
+// the exponents reduced exactly (k_a f_a mod n) and read from the twiddle table.
+// Pieces are staged in LDS in chunks; one thread per bin.
 constexpr int PATH_CHUNK = 128;
 
 template <typename S>
@@ -2186,9 +2189,10 @@ __global__ __launch_bounds__(256) void k_path_spectrum(const DevPiece* __restric
 //
 // One thread per piece and grid point around it.  The points in use get a
 // record each (map: the voxel's record, claimed by whichever comes first);
-// contributions are added there in fixed point, each value's low 32 bits and
-// the rest in sums of their own, so that the result is exact to 2^-62 of the
-// largest piece and does not depend on the order.
+// contributions, products rounded to FP64, are added there in fixed point, 2^-61
+// of the largest piece's power of two, each value's low 32 bits and the rest in
+// sums of their own: the sums are exact and do not depend on the order, and are
+// rounded to FP64 once.
 __global__ __launch_bounds__(256) void k_piece_points(const DevPiece* __restrict__ pieces, int np, int n, double scale,
                                                       int32_t* __restrict__ map, int64_t* __restrict__ sums) {
   const int t = blockIdx.x * 256 + threadIdx.x;
