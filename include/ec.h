@@ -135,7 +135,8 @@ EC_API ec_status ec_ctx_create(int device, size_t hbm_budget_bytes, ec_alloc_fn 
 /* Destroy every state of a context before the context itself. */
 EC_API void ec_ctx_destroy(ec_ctx* ctx);
 
-/* Bytes the context has admitted so far, and its budget. */
+/* Bytes the context has admitted so far, and its budget (scratch kept between
+ * calls, which gives way to allocations, not counted). */
 EC_API ec_status ec_ctx_ledger(const ec_ctx* ctx, size_t* used, size_t* budget);
 
 /* Number of executable HIP graphs the context holds for batched hops
@@ -343,7 +344,15 @@ typedef struct {
  * stiffness and frame, and the stress is kept as a background added to the
  * resident stress of this and every later solve, as for ec_set_dislocations
  * (both kinds may be present).  At most 2^20 pieces in all; finite values,
- * |b| > 0 (EC_ERR_ARG otherwise).  Synchronises the stream. */
+ * |b| > 0 (EC_ERR_ARG otherwise).  Synchronises the stream.
+ * From some hundred pieces on the spectrum is formed by transforms of the spread
+ * Nye tensor, with two FP64 half spectra of scratch (0.43 GB at n = 160, 13 GB
+ * at 512) that the context lends to one call at a time.  They are charged to
+ * the ledger while the call runs (allocations of other threads wait for them
+ * rather than fail) and kept for the next call up to an eighth of the budget,
+ * uncharged, until another allocation of the context needs the memory.  Where
+ * budget or memory do not hold them the pieces are summed at every bin instead:
+ * the same stress to rounding, not to the last bit. */
 EC_API ec_status ec_set_dislocation_paths(ec_state* st, const ec_path* paths, int32_t npaths, const double* verts,
                                           int32_t nverts, void* hip_stream);
 

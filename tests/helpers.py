@@ -28,3 +28,14 @@ def energy_ok_fp32(E, Eref):
 def energy_ok_fp64(E, Eref, rtol=1e-10):
     """Normwise FP64 criterion: max |E - Eref| <= rtol * max |Eref|."""
     return float(np.max(np.abs(E - Eref))) <= rtol * float(np.max(np.abs(Eref)))
+
+
+def kernels_of(call):
+    """Names of the GPU kernels that ran during call(), one text."""
+    import torch
+    from torch.profiler import ProfilerActivity, profile
+
+    with profile(activities=[ProfilerActivity.CUDA]) as p:
+        call()
+        torch.cuda.synchronize()
+    return "\n".join(e.key for e in p.key_averages())

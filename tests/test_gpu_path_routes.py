@@ -1,0 +1,164 @@
+"""Dislocation paths by their two routes. The grid's scratch is kept by the
+context for the next call, outside the ledger between calls, makes room for other
+allocations, and while a call has it another thread's allocation waits for it."""
+import threading
+import time
+
+import numpy as np
+import pytest
+
+from helpers import kernels_of, rel_l2
+from paper_2403_09158_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+SUMS, GRID = "k_path_spectrum", "k_piece_points"
+
+
+def _squares(n, pieces):
+    """Square loops cut into `pieces` pieces (a multiple of four) together."""
+    h = inputs.H_VOXEL
+    rng = np.random.default_rng(pieces)
+    out = []
+    while pieces > 0:
+        k = min(5, pieces // 4)
+        c = rng.uniform(0.0, n * h, 3)
+        v = c + k * h * np.array([[0.0, 0.0, 0.0], [1.0, 0.0, 0.0], [1.0, 1.0, 0.0], [0.0, 1.0, 0.0]])
+        out.append((v, np.zeros(3), inputs.A_FE * rng.normal(size=3)))
+        pieces -= 4 * k
+    return out
+
+
+def _state(ctx, n, prec=0):
+    from paper_2403_09158_amd import ec
+
+    h = inputs.H_VOXEL
+    st = ec.State(ctx, inputs.Problem(n, n * h, *inputs.CUBIC_FE, prec=prec, bc=1))
+    return st
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+def test_direct_radix(prec):
+    """129: the grid against the sums of a context without room for its scratch."""
+    from paper_2403_09158_amd import ec
+
+    n = 129
+    paths = _squares(n, 160)
+    fields, budget = [], 0
+    for route, other in ((GRID, SUMS), (SUMS, GRID)):
+        ctx = ec.Context(0, budget_bytes=budget)
+        st = _state(ctx, n, prec)
+        st.solve(inputs.sphere(np.full(3, 0.4 * n * inputs.H_VOXEL), 0.7, 0.01))
+        names = kernels_of(lambda: st.set_dislocation_paths(paths))
+        assert route in names and other not in names
+        budget = ctx.ledger()[0] + 6 * n**3 * 8 + 65536  # room for a field's copy only
+        fields.append(st.field("sigma"))
+        st.close()
+        ctx.close()
+    assert rel_l2(fields[0], fields[1]) < (1e-12 if prec == 0 else 1e-5)
+
+
+class _Hooks:
+    """Torch-backed allocation hooks that note the sizes asked for."""
+
+    def __init__(self):
+        import torch
+
+        self._alloc, self._delete = torch.cuda.caching_allocator_alloc, torch.cuda.caching_allocator_delete
+        self.sizes, self.live = [], {}
+
+    def alloc(self, nbytes):
+        self.sizes.append(nbytes)
+        p = self._alloc(nbytes)
+        self.live[p] = nbytes
+        return p
+
+    def free(self, ptr):
+        del self.live[ptr]
+        self._delete(ptr)
+
+
+def test_scratch_is_kept_and_gives_way():
+    from paper_2403_09158_amd import ec
+
+    n = 64
+    big = 2 * 6 * n * n * 40 * 16  # two FP64 half spectra of 64^3
+    paths = [_squares(n, 400), _squares(n, 360)]
+    h = _Hooks()
+    ctx = ec.Context(0, hooks=(h.alloc, h.free))
+    st = _state(ctx, n, 1)
+    st.solve(inputs.empty_defects(0))
+    st.set_dislocation_paths(paths[0])
+    used = ctx.ledger()[0]
+    ref = st.field("sigma")
+    assert max(h.sizes) >= big and sum(h.live.values()) >= used + big
+    h.sizes.clear()
+    for p in (paths[1], paths[0]):
+        st.set_dislocation_paths(p)
+    assert max(h.sizes) < big
+    assert ctx.ledger()[0] == used
+    assert np.array_equal(st.field("sigma"), ref)  # the same route, the same bits
+    st.close()
+    ctx.close()
+    assert not h.live
+
+    # a budget that holds a state and the scratch, or two states
+    h = _Hooks()
+    ctx = ec.Context(0, budget_bytes=8 * (used + big) + (1 << 20), hooks=(h.alloc, h.free))
+    st = _state(ctx, n, 1)
+    st.solve(inputs.empty_defects(0))
+    st.set_dislocation_paths(paths[0])
+    kept = sum(h.live.values()) - ctx.ledger()[0]
+    assert kept >= big
+    more = []
+    while ctx.ledger()[1] - ctx.ledger()[0] >= used:  # the budget filled: the idle scratch goes
+        more.append(_state(ctx, n, 1))
+    assert sum(h.live.values()) - ctx.ledger()[0] < kept
+    st.set_dislocation_paths(paths[0])  # no room left: the sums
+    assert rel_l2(st.field("sigma"), ref) < 1e-5
+    for s in (st, *more):
+        s.close()
+    ctx.close()
+    assert not h.live
+
+
+def test_other_threads_wait_for_the_scratch():
+    from paper_2403_09158_amd import ec
+
+    n = 96
+    paths = _squares(n, 2000)
+    probe = ec.Context(0)
+    st = _state(probe, n, 1)
+    one = probe.ledger()[0]
+    st.solve(inputs.empty_defects(0))
+    st.set_dislocation_paths(paths)
+    st.set_dislocation_paths(paths)
+    used = probe.ledger()[0]
+    st.close()
+    probe.close()
+    scratch = 2 * 6 * n * n * 56 * 16 + n**3 * 4 + 2000 * 1920 + (1 << 20)
+    ctx = ec.Context(0, budget_bytes=used + max(scratch, one) + 2000 * 200)  # the scratch or another state, not both
+    st = _state(ctx, n, 1)
+    st.solve(inputs.empty_defects(0))
+    st.set_dislocation_paths(paths)
+    stop, errors = threading.Event(), []
+
+    def calls():
+        try:
+            while not stop.is_set():
+                st.set_dislocation_paths(paths, stream=0)
+        except Exception as e:  # reported by the test's thread
+            errors.append(e)
+
+    t = threading.Thread(target=calls)
+    t.start()
+    try:
+        for pause in np.random.default_rng(1).uniform(0.0, 2e-3, 100):  # at any time of a call
+            time.sleep(pause)
+            _state(ctx, n, 1).close()
+    finally:
+        stop.set()
+        t.join()
+    assert not errors
+    st.close()
+    ctx.close()
