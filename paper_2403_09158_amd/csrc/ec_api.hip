@@ -2846,10 +2846,22 @@ ec_status ec_set_dislocations(ec_state* st, const ec_line* lines, int32_t nlines
   return EC_OK;
 }
 
-// Pieces from which on the paths' spectrum is formed on the grid (below, the sum
-// over the pieces at every bin takes less than the transforms), and up to which
-// its scratch is asked for (2 KB a piece beside two FP64 half spectra).
-constexpr size_t PATH_POINTS_MIN = 96, PATH_POINTS_MAX = 131072;
+// Pieces from which on the paths' spectrum is formed on the grid, where the sum
+// over the pieces at every bin takes as long as the transforms do.  us per call,
+// sums / grid (FP32 states; FP64 ones cross at the same counts): 32^3 126 pieces
+// 111 / 119, 168 120 / 118 (launches); 48^3 210 144 / 154, 336 185 / 162; 64^3 84
+// 138 / 163, 126 165 / 167, 168 189 / 168; 96^3 84 241 / 249, 126 300 / 250; 160^3
+// 84 835 / 796; 256^3 84 3161 / 3229, 126 4103 / 3228; with a direct radix in the
+// transforms, 129^3 126 793 / 890, 168 919 / 890.
+size_t path_points_min(int n) {
+  if (n < 40) return 160;
+  if (n < 56) return 240;
+  if (n < 80) return 128;
+  return direct_length(n) ? 160 : 96;
+}
+// Pieces up to which its scratch is asked for (2 KB a piece beside two FP64 half
+// spectra).
+constexpr size_t PATH_POINTS_MAX = 131072;
 
 ec_status ec_set_dislocation_paths(ec_state* st, const ec_path* paths, int32_t npaths, const double* verts,
                                    int32_t nverts, void* stream) {
@@ -2949,7 +2961,7 @@ ec_status ec_set_dislocation_paths(ec_state* st, const ec_path* paths, int32_t n
   double mmax = 0.0;
   for (const DevPiece& pc : pieces)
     for (double v : pc.M) mmax = std::max(mmax, std::fabs(v));
-  bool points = pieces.size() >= PATH_POINTS_MIN && pieces.size() <= PATH_POINTS_MAX && mmax > 0.0 &&
+  bool points = pieces.size() >= path_points_min(n) && pieces.size() <= PATH_POINTS_MAX && mmax > 0.0 &&
                 std::ilogb(mmax) > -900 && std::ilogb(mmax) < 900;
   if (points && ts.take(path_scratch(n, (int)pieces.size()).bytes) != EC_OK) points = false;
   HIPCHK(hipStreamSynchronize(s));
