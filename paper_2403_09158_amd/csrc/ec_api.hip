@@ -1670,6 +1670,7 @@ ec_status solve_table(ec_state* st, DevDefect* h, int32_t ndef, hipStream_t s, b
   std::vector<DevDefect> list;
   if (early) {
     list.assign(h, h + ndef);
+    st->classes_ok = false;  // until the list is in place: the old one's are assigned again if this call fails
     renew_classes(st, list);
     for (int i = 0; i < ndef; ++i) {
       h[i].cls = list[i].cls;
