@@ -1626,9 +1626,13 @@ bool sparse_rows(const ec_state* st) { return st->fp64 && st->volume < rows_limi
 // Cells and lists up to which the self terms go before the passes (solve_table).
 // The classes are then assigned on the host before the first launch (about 10 ns
 // a defect, none of it hidden), which pays while the x and y passes are too short
-// to hide the self terms: FP64 96^3, 600 defects 219 us early against 227, 1000
-// defects 249 against 245; 128^3, 1000 defects 312 against 294, 2500 449 against 402.
-constexpr int64_t EARLY_SELF_VOXELS = 128 * 128 * 128;
+// to hide the self terms.  us per solve with energies, FP32 and FP64 alike, late /
+// early, two runs: 32^3 50 defects 166 / 116, 2000 363 / 309; 48^3 1000 344 / 293,
+// 6000 1030 / 1062; 64^3 200 246 / 187, 2500 520 / 495; 96^3 100 180 / 168, 800
+// 244 / 222, 1200 265 / 255 and 272 / 268; at 128^3 nothing is gained (50 defects
+// 190 / 192, 300 236 / 236, 1000 278 / 280), from 129^3 on it is slower (160^3 300
+// 308 / 334).
+constexpr int64_t EARLY_SELF_VOXELS = 96 * 96 * 96;
 constexpr int64_t EARLY_SELF_WORK = 700LL * 1000 * 1000;  // defects x voxels: 800 defects at 96^3
 
 // Commits the quantised list h (ndef entries in the pinned staging buffer of
