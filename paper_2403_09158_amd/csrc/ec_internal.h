@@ -474,10 +474,14 @@ hipError_t launch_reduce(const DevDefect* d, int ndef, const int32_t* counts, co
 hipError_t launch_window_crop(const double* sig, int n, int D, int b, double* K, hipStream_t s);
 hipError_t launch_class_windows(const double* K, int D, const double* dirs, int ncls, double* g, hipStream_t s);
 // Pairs per work item of the pair sums.  Short lists take a quarter of them
-// (SELF_PAIRS_FEW) while their items stay below SELF_FEW_ITEMS, a few per
-// resident workgroup: an item's pairs are one serial chain of gathers per lane,
-// and with few items that chain is the kernel's time (200 defects on 64^3, 40 of
-// them on the pair path: 53 -> 19 us).
+// (SELF_PAIRS_FEW) while their items stay below SELF_FEW_ITEMS: an item's pairs
+// are one serial chain of gathers per lane, and with few items that chain is the
+// kernel's time (200 defects on 64^3, 40 of them on the pair path: 53 -> 19 us).
+// All kernels of the self terms, us, long / short items, two runs: 64^3 50
+// defects 34 / 34, 200 102 / 85, 1000 117 / 122; 96^3 400 43 / 44; 128^3 300
+// 45 / 47; 256^3 2000 104 / 93.  Long lists gain nothing that a solve shows
+// (512^3, 20000 defects 10.6 ms either way), so the limit keeps their work lists
+// short.
 constexpr double SELF_PAIRS = 32768.0, SELF_PAIRS_FEW = 8192.0;
 constexpr int64_t SELF_FEW_ITEMS = 8192;
 // Self-term work item: rows [p0, p1) of defect `def`'s pair triangle.

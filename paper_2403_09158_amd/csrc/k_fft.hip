@@ -452,7 +452,7 @@ __global__ __launch_bounds__(pick_T(max_nb(N, 3 * x_rows(N)))) void k_x_forward(
 // FP64 storage only: with FP32 storage a last-bit difference from the
 // transforms moves the rounding of a spectrum value now and then, and the
 // later passes spread that over the whole field at the level of the storage
-// error.  At 129^3, 300 defects, the pass takes 19 us (transforms: 170, bound by
+// error.  At 129^3, 300 defects, the pass takes 19 us (transforms: 116, bound by
 // the length-43 butterflies), at 256^3, 2000 defects, 222 (236; 811 MB written).
 template <int N>
 __global__ __launch_bounds__(256) void k_x_forward_rows(const int32_t* __restrict__ own, const int2* __restrict__ lnk,
@@ -1751,7 +1751,9 @@ bool direct_length(int n) { return has_direct(plan_of(n)); }
 // 2.1 and 4.2 % covered: 256^3 188 / 222, 222 / 236, 234 / 260; at 3.2 % of
 // 240^3 204 / 225; past that the transforms win (6.4 % of 160^3: 65 / 61, 21 %
 // of 128^3: 50 / 42).  Where the transform has a direct large radix the sums win
-// by far (129^3: 21 / 171 at 0.6 %, 32 / 175 at 5 %).
+// by far (129^3: 19 / 116 at 0.6 %; balls of 12 voxels: 35 / 117 at 5 % of the
+// cell, 66 / 125 at 20, 98 / 137 at 40, 123 / 151 at 55, 140 / 160 at 70, 193 / 177
+// at 100, overlaps counted once per ball).
 double rows_limit(int n) { return direct_length(n) ? 0.5 : 0.04; }
 
 int pencil_width(int n, bool) { return n >= 512 ? 8 : 16; }

@@ -25,9 +25,9 @@ ROWS, TRANSFORMS = "k_x_forward_rows<", "k_x_forward<"
         (64, (13.5,), ROWS),  # 10306
         (64, (13.65,), TRANSFORMS),  # 10653
         (64, (19.0, 12.0, 9.0), TRANSFORMS),
-        (129, (38.7, 20.0), ROWS),  # 13 %
-        (129, (51.6, 52.0), TRANSFORMS),  # 54 %, most of it twice
-        (160, (48.0,), TRANSFORMS),
+        (129, (24.5,) * 16, ROWS),  # 46 %
+        (129, (24.5,) * 20, TRANSFORMS),  # 57 %, nearly all of it twenty times over
+        (160, (24.5,) * 4, TRANSFORMS),  # 6 %
     ],
 )
 def test_solve_against_oracle(n, radii, route):
