@@ -179,3 +179,45 @@ def test_other_threads_wait_for_the_scratch():
     assert not errors
     st.close()
     ctx.close()
+
+
+def test_several_threads_take_turns():
+    """Four states on streams of their own set paths at once: the fields of one
+    after another (to rounding: an exchange takes the old paths' stress out again)."""
+    import torch
+
+    from paper_2403_09158_amd import ec
+
+    n, k = 64, 4
+    ctx = ec.Context(0)
+    sts = [_state(ctx, n) for _ in range(k)]
+    sets = [[_squares(n, 200 + 100 * j), _squares(n, 700 - 100 * j)] for j in range(k)]
+    refs = []
+    for st, ps in zip(sts, sets):
+        st.solve(inputs.empty_defects(0))
+        for p in ps:
+            st.set_dislocation_paths(p)
+        refs.append(st.field("sigma"))
+    errors = []
+
+    def calls(st, ps):
+        try:
+            s = torch.cuda.Stream()
+            for _ in range(10):
+                st.solve(inputs.empty_defects(0), stream=s)
+                for p in ps:
+                    st.set_dislocation_paths(p, stream=s)
+        except Exception as e:  # reported by the test's thread
+            errors.append(e)
+
+    threads = [threading.Thread(target=calls, args=a) for a in zip(sts, sets)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not errors
+    for st, ref in zip(sts, refs):
+        st.solve(inputs.empty_defects(0))
+        assert rel_l2(st.field("sigma"), ref) < 1e-14
+        st.close()
+    ctx.close()
